@@ -33,14 +33,9 @@ typedef uint32_t u2 __attribute__((ext_vector_type(2)));
 // A whole tile is moved with every load of a thread issued before the first
 // LDS write (9 elements per thread), nontemporal loads and stores, and, in
 // FP64, the XCD-contiguous tile order (each XCD one contiguous eighth of the
-// tiles; a one-pass grid). Against element-at-a-time loops with plain
-// accesses in tile = workgroup index order (random data, AoS -> SoA / SoA ->
-// AoS, TB/s): FP64 L=48 5.30 / 5.75 against 5.31 / 5.62, L=32 5.65 / 5.85
-// against 5.16 / 5.47; FP32 (workgroup order: the XCD order was 0-6% slower
-// there) L=48 5.64 / 5.96 against 5.33 / 5.54, L=32 6.06 / 5.80 against
-// 5.04 / 5.15. 128- and 64-thread workgroups, 32-site tiles and loads in
-// three phases were within 2% either way or slower. The last, ragged tile
-// moves element by element.
+// tiles; a one-pass grid). The last, ragged tile moves element by element.
+// This is the path of the small lattices (and of any too large for the
+// one-pass grids below); launch_aos_soa has the rule.
 constexpr int kTileSites = 64;
 
 template <typename V, bool kToSoa, bool kXcd>
@@ -121,6 +116,201 @@ __global__ __launch_bounds__(kBlock) void transpose_aos_soa(const V *__restrict_
                 dst[s0 * 36 + e] = tile[e % 36][e / 36];
         }
         __syncthreads();
+    }
+}
+
+// The same transforms for the larger lattices, one tile of TS sites per
+// workgroup of B threads, tile = workgroup index. What bounds them is the 36
+// plane streams: a kernel that only copies the same addresses (36 KiB per
+// workgroup in and out, no LDS) peaks at 6.0 (to planes) and 6.2 TB/s (from
+// planes) at 2,560,000 FP64 sites, with one such workgroup per CU, and falls
+// to 5.6 and 5.9 with two to four; the run length on the planes (1 to 16 KiB)
+// does not matter. So the tile and the number of resident workgroups set the
+// bytes in flight, and many threads with few elements each keep a tile's
+// life short. launch_aos_soa states which tile serves which size.
+//
+// kHalo, for planes that do not start on 128-byte lines (a site count that
+// is no multiple of 8 in FP64 or 16 in FP32, dense): a run cut at the tile's
+// own sites would begin and end inside a line that the neighbouring
+// workgroup writes too, and two partial writes of a line cost far more than
+// one whole one (at 31^4 sites 4.4 TB/s in FP64 and 3.7 in FP32, and 5.5 and
+// 5.1 with the halo). The workgroup instead reads
+// one line's worth of sites past its tile and moves each plane's window up to
+// that plane's next line boundary, so that every line is written whole by one
+// workgroup; the first tile also writes the sites before its window.
+template <typename V, int TS, int B, bool kHalo>
+__global__ __launch_bounds__(B) void to_soa_tile(const V *__restrict__ src, V *__restrict__ dst, int64_t n,
+                                                 int64_t pitch)
+{
+    constexpr int H = kHalo ? 128 / (int)sizeof(V) : 1;   // sites per line
+    constexpr int W = kHalo ? TS + H : TS;                // sites read
+    constexpr int kIn = (36 * W + B - 1) / B, kOut = 36 * TS / B;
+    static_assert(kOut * B == 36 * TS && TS % H == 0, "a tile splits evenly over the workgroup and into lines");
+    __shared__ V tile[36][W + 1];
+    const int64_t s0 = (int64_t)blockIdx.x * TS, nin = n * 36;
+    V v[kIn];
+#pragma unroll
+    for (int i = 0; i < kIn; ++i) {
+        const int e = threadIdx.x + i * B;
+        const int64_t g = s0 * 36 + e;
+        if (36 * W % B == 0 || e < 36 * W)
+            v[i] = ld_stream(src + (g < nin ? g : nin - 1));   // in bounds; unused past the end
+    }
+#pragma unroll
+    for (int i = 0; i < kIn; ++i) {
+        const int e = threadIdx.x + i * B;
+        if (36 * W % B == 0 || e < 36 * W)
+            tile[e % 36][e / 36] = v[i];
+    }
+    __syncthreads();
+    // sites from s0 up to plane p's next line boundary
+    const unsigned at = kHalo ? (unsigned)(((uintptr_t)dst / sizeof(V) + (uint64_t)s0) % H) : 0;
+    const unsigned step = kHalo ? (unsigned)(pitch % H) : 0;
+    auto shift = [=](int p) { return (int)((H - (at + (unsigned)p * step) % H) % H); };
+    V o[kOut];
+#pragma unroll
+    for (int i = 0; i < kOut; ++i) {
+        const int e = threadIdx.x + i * B, p = e / TS;
+        o[i] = tile[p][e % TS + shift(p)];
+    }
+#pragma unroll
+    for (int i = 0; i < kOut; ++i) {
+        const int e = threadIdx.x + i * B, p = e / TS;
+        const int64_t s = s0 + e % TS + shift(p);
+        if (s < n)
+            st_stream(dst + (int64_t)p * pitch + s, o[i]);
+    }
+    if (kHalo && blockIdx.x == 0) {
+        for (int e = threadIdx.x; e < 36 * H; e += B) {
+            const int p = e / H, s = e % H;
+            if (s < shift(p) && s < n)
+                dst[(int64_t)p * pitch + s] = tile[p][s];
+        }
+    }
+}
+
+// kNt: nontemporal plane loads. Where planes do not start on lines, two
+// workgroups read the line at a tile's edge, and FP32 keeps it in the cache.
+template <typename V, int TS, int B, bool kNt>
+__global__ __launch_bounds__(B) void to_aos_tile(const V *__restrict__ src, V *__restrict__ dst, int64_t n,
+                                                 int64_t pitch)
+{
+    constexpr int kPer = 36 * TS / B;
+    static_assert(kPer * B == 36 * TS, "a tile splits evenly over the workgroup");
+    __shared__ V tile[36][TS + 1];
+    const int64_t s0 = (int64_t)blockIdx.x * TS, nout = n * 36;
+    V v[kPer];
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) {
+        const int e = threadIdx.x + i * B;
+        const int64_t s = s0 + e % TS;
+        const V *q = src + (int64_t)(e / TS) * pitch + (s < n ? s : n - 1);   // in bounds; unused past the end
+        v[i] = kNt ? ld_stream(q) : *q;
+    }
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) {
+        const int e = threadIdx.x + i * B;
+        tile[e / TS][e % TS] = v[i];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) {
+        const int e = threadIdx.x + i * B;
+        v[i] = tile[e % 36][e / 36];
+    }
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) {
+        const int64_t g = s0 * 36 + threadIdx.x + i * B;
+        if (g < nout)
+            st_stream(dst + g, v[i]);
+    }
+}
+
+// FP32 with both sides in 16-byte accesses: two elements of a site on the
+// site-major side, two sites of a plane on the plane side (every plane on a
+// 128-byte boundary, so pairs of sites are 16-byte aligned). Half the
+// memory instructions of 8-byte elements: 7.2 against 10.5 us at 65,536
+// sites. Padding is neither read nor written.
+template <int TS, int B>
+__global__ __launch_bounds__(B) void to_soa_pairs(const f4 *__restrict__ src, f2 *__restrict__ dst, int64_t n,
+                                                  int64_t pitch)
+{
+    constexpr int kPer = 18 * TS / B;
+    static_assert(kPer * B == 18 * TS && TS % 2 == 0, "a tile splits evenly over the workgroup");
+    __shared__ __attribute__((aligned(16))) f2 tile[36][TS + 2];   // even rows keep pairs aligned
+    const int64_t s0 = (int64_t)blockIdx.x * TS, nin = n * 18;
+    f4 v[kPer];
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) {
+        const int64_t g = s0 * 18 + threadIdx.x + i * B;
+        v[i] = ld_stream(src + (g < nin ? g : nin - 1));   // in bounds; unused past the end
+    }
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) {
+        const int e = 2 * (threadIdx.x + i * B);
+        tile[e % 36][e / 36] = f2{v[i].x, v[i].y};
+        tile[e % 36 + 1][e / 36] = f2{v[i].z, v[i].w};
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) {
+        const int e = 2 * (threadIdx.x + i * B);
+        v[i] = *reinterpret_cast<const f4 *>(&tile[e / TS][e % TS]);
+    }
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) {
+        const int e = 2 * (threadIdx.x + i * B);
+        const int64_t s = s0 + e % TS;
+        f2 *q = dst + (int64_t)(e / TS) * pitch + s;
+        if (s + 1 < n)
+            st_stream(reinterpret_cast<f4 *>(q), v[i]);
+        else if (s < n)
+            *q = f2{v[i].x, v[i].y};
+    }
+}
+
+template <int TS, int B>
+__global__ __launch_bounds__(B) void to_aos_pairs(const f2 *__restrict__ src, f4 *__restrict__ dst, int64_t n,
+                                                  int64_t pitch)
+{
+    constexpr int kPer = 18 * TS / B;
+    static_assert(kPer * B == 18 * TS && TS % 2 == 0, "a tile splits evenly over the workgroup");
+    __shared__ __attribute__((aligned(16))) f2 tile[36][TS + 2];
+    const int64_t s0 = (int64_t)blockIdx.x * TS, nout = n * 18;
+    f4 v[kPer];
+    if (s0 + TS <= n) {
+#pragma unroll
+        for (int i = 0; i < kPer; ++i) {
+            const int e = 2 * (threadIdx.x + i * B);
+            v[i] = ld_stream(reinterpret_cast<const f4 *>(src + (int64_t)(e / TS) * pitch + s0 + e % TS));
+        }
+    } else {
+#pragma unroll
+        for (int i = 0; i < kPer; ++i) {
+            const int e = 2 * (threadIdx.x + i * B);
+            const int64_t s = s0 + e % TS;
+            const f2 *q = src + (int64_t)(e / TS) * pitch;
+            const f2 x = q[s < n ? s : n - 1], y = q[s + 1 < n ? s + 1 : n - 1];
+            v[i] = f4{x.x, x.y, y.x, y.y};
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) {
+        const int e = 2 * (threadIdx.x + i * B);
+        *reinterpret_cast<f4 *>(&tile[e / TS][e % TS]) = v[i];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) {
+        const int e = 2 * (threadIdx.x + i * B);
+        const f2 x = tile[e % 36][e / 36], y = tile[e % 36 + 1][e / 36];
+        v[i] = f4{x.x, x.y, y.x, y.y};
+    }
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) {
+        const int64_t g = s0 * 18 + threadIdx.x + i * B;
+        if (g < nout)
+            st_stream(dst + g, v[i]);
     }
 }
 
@@ -352,22 +542,98 @@ static unsigned grid_for(int64_t items, int64_t per_block, int64_t cap = kOnePas
     return (unsigned)g;
 }
 
+// K on tiles of TS sites, one workgroup of B threads each, at most kPerCU
+// workgroups resident per CU (0: as many as fit).
+template <auto K, int TS, int B, int kPerCU, typename VS, typename VD>
+static hipError_t launch_tiles(const VS *src, VD *dst, int64_t n, int64_t pitch, hipStream_t s)
+{
+    static std::atomic<int> cache[kMaxDevices];
+    const size_t pad = occupancy_pad(reinterpret_cast<const void *>(K), kPerCU * (B / 64), B, cache);
+    return launch_k(K, dim3((unsigned)((n + TS - 1) / TS)), dim3(B), s, pad, src, dst, n, pitch);
+}
+template <typename V, int TS, int B, bool kHalo, int kPerCU>
+static hipError_t launch_to_soa(const void *src, void *dst, int64_t n, int64_t pitch, hipStream_t s)
+{
+    return launch_tiles<to_soa_tile<V, TS, B, kHalo>, TS, B, kPerCU>((const V *)src, (V *)dst, n, pitch, s);
+}
+template <typename V, int TS, int B, bool kNt, int kPerCU>
+static hipError_t launch_to_aos(const void *src, void *dst, int64_t n, int64_t pitch, hipStream_t s)
+{
+    return launch_tiles<to_aos_tile<V, TS, B, kNt>, TS, B, kPerCU>((const V *)src, (V *)dst, n, pitch, s);
+}
+// The general path: any size, a grid of 64-site tiles that loops past kOnePass.
+template <typename V, bool kXcd>
+static hipError_t launch_general(const void *src, void *dst, int64_t n, int64_t pitch, bool to_soa, hipStream_t s)
+{
+    const dim3 g(grid_for(n, kTileSites));
+    if (to_soa)
+        return launch_k(transpose_aos_soa<V, true, kXcd>, g, dim3(kBlock), s, 0, (const V *)src, (V *)dst, n, pitch);
+    return launch_k(transpose_aos_soa<V, false, kXcd>, g, dim3(kBlock), s, 0, (const V *)src, (V *)dst, n, pitch);
+}
+
+// Which transpose serves which lattice (microseconds, this path / the general
+// one, on random data in rotating buffers). `lines`: every plane starts on a
+// 128-byte line.
+//  FP64, up to 49,152 sites: the general path; its 64-site tiles give more CUs
+//    work than larger ones, and its XCD order collides less at 2^15 sites.
+//  FP64 to planes, on lines: up to 65,536 sites 128-site tiles, the whole grid
+//    resident at two per CU (65,536: 13.3 / 15.6); above, 32-site tiles of
+//    576 threads (24^4: 64 / 78, 40^4: 500 / 565, 48^4: 1054 / 1150; 1.05 to
+//    1.21 times as fast at 20 sizes and pitches). Off lines, 128-site tiles with
+//    the halo, two per CU up to 131,072 sites (65,537: 13.5 / 15.9) and one
+//    above (31^4: 193 / 250, 2,560,001: 533 / 630).
+//  FP64 from planes, on lines: up to 65,536 sites as above; up to 196,608
+//    32-site tiles (160,000: 32.4 / 35.2); above, 128-site tiles, one per CU
+//    (24^4: 64 / 72, 40^4: 478 / 523, 48^4: 996 / 1074; 1.03 to 1.15 at 20
+//    sizes and pitches), whose last generation of workgroups costs too much
+//    on fewer tiles. Off lines the general path up to 196,608 sites and these
+//    tiles above (31^4: 177 / 208).
+//  FP32 on lines: pairs; 64-site tiles of 128 threads up to 131,072 sites
+//    (65,536: 7.2 / 10.5); above, 576 threads on 64 sites to planes (40^4: 243
+//    / 257, 48^4: 516 / 558; 1.02 to 1.10 at 20 sizes and pitches). From
+//    planes, 128-site pairs where the plane stride is a multiple of 4 MiB
+//    and the planes collide (2^20: 97 / 105, 1.08 to 1.10) and single
+//    elements on 64-site tiles of 768 threads elsewhere (1.00 to 1.05; pairs
+//    lost up to 3% there).
+//  FP32 off lines: up to 49,152 sites the general path; above, 128-site tiles
+//    of 256 threads, to planes with the halo, two per CU (65,537: 9.3 / 10.7,
+//    31^4: 105 / 142, 2,560,001: 266 / 381), from planes with cached loads
+//    (65,537: 8.6 / 11.1, 31^4: 94 / 105, 2,560,001: 251 / 280).
+//  Over 2^27 sites, where a one-pass grid could pass 2^32 threads: the general
+//    path, which loops.
 hipError_t launch_aos_soa(const void *src, void *dst, int64_t sites, int64_t pitch, int elem_bytes, bool to_soa,
                           hipStream_t s)
 {
-    const unsigned g = grid_for(sites, kTileSites);
+    const int64_t n = sites;
+    const bool lines = pitch * elem_bytes % 128 == 0 && (uintptr_t)(to_soa ? dst : src) % 128 == 0;
+    const bool huge = n > (int64_t)1 << 27;
     if (elem_bytes == 16) {
+        if (n <= 49152 || huge || (!to_soa && !lines && n <= 196608))
+            return launch_general<d2, true>(src, dst, n, pitch, to_soa, s);
+        if (to_soa && !lines)
+            return n <= 131072 ? launch_to_soa<d2, 128, 768, true, 0>(src, dst, n, pitch, s)
+                               : launch_to_soa<d2, 128, 768, true, 1>(src, dst, n, pitch, s);
         if (to_soa)
-            return launch_k(transpose_aos_soa<d2, true, true>, dim3(g), dim3(kBlock), s, 0, (const d2 *)src, (d2 *)dst,
-                            sites, pitch);
-        return launch_k(transpose_aos_soa<d2, false, true>, dim3(g), dim3(kBlock), s, 0, (const d2 *)src, (d2 *)dst,
-                        sites, pitch);
+            return n <= 65536 ? launch_to_soa<d2, 128, 768, false, 0>(src, dst, n, pitch, s)
+                              : launch_to_soa<d2, 32, 576, false, 0>(src, dst, n, pitch, s);
+        if (n <= 65536)
+            return launch_to_aos<d2, 128, 768, true, 0>(src, dst, n, pitch, s);
+        return n <= 196608 ? launch_to_aos<d2, 32, 576, true, 0>(src, dst, n, pitch, s)
+                           : launch_to_aos<d2, 128, 768, true, 1>(src, dst, n, pitch, s);
     }
+    if (huge || (!lines && n <= 49152))
+        return launch_general<f2, false>(src, dst, n, pitch, to_soa, s);
+    if (!lines)
+        return to_soa ? launch_to_soa<f2, 128, 256, true, 2>(src, dst, n, pitch, s)
+                      : launch_to_aos<f2, 128, 256, false, 0>(src, dst, n, pitch, s);
+    if (n <= 131072)
+        return to_soa ? launch_tiles<to_soa_pairs<64, 128>, 64, 128, 0>((const f4 *)src, (f2 *)dst, n, pitch, s)
+                      : launch_tiles<to_aos_pairs<64, 128>, 64, 128, 0>((const f2 *)src, (f4 *)dst, n, pitch, s);
     if (to_soa)
-        return launch_k(transpose_aos_soa<f2, true, false>, dim3(g), dim3(kBlock), s, 0, (const f2 *)src, (f2 *)dst,
-                        sites, pitch);
-    return launch_k(transpose_aos_soa<f2, false, false>, dim3(g), dim3(kBlock), s, 0, (const f2 *)src, (f2 *)dst,
-                    sites, pitch);
+        return launch_tiles<to_soa_pairs<64, 576>, 64, 576, 0>((const f4 *)src, (f2 *)dst, n, pitch, s);
+    return pitch * 8 % ((int64_t)4 << 20) == 0
+               ? launch_tiles<to_aos_pairs<128, 576>, 128, 576, 0>((const f2 *)src, (f4 *)dst, n, pitch, s)
+               : launch_to_aos<f2, 64, 768, true, 0>(src, dst, n, pitch, s);
 }
 
 hipError_t launch_stream_copy(const void *src, void *dst, int64_t bytes, hipStream_t s)

@@ -11,7 +11,8 @@
 //    1 KiB runs and is transposed to one unit per lane through LDS (fwd_aos).
 //  * Structure-of-arrays: a thread owns one (site, output row); every plane
 //    access of a wavefront is already one contiguous run, and the row is
-//    uniform over a workgroup, so b[j] sits in scalar registers (fwd_soa).
+//    uniform over a workgroup, so b[j] sits in scalar registers (fwd_soa;
+//    fwd_soa_halo where the output planes start off 128-byte lines).
 //  * The grid covers the lattice once: each wavefront streams one tile and
 //    exits. In the site-major kernels each XCD takes one contiguous eighth of
 //    the tiles (xcd_tile); the SoA kernel picks its order (soa_xcd) and, in
@@ -526,6 +527,76 @@ __global__ __launch_bounds__(kSoaBlock) void fwd_soa(const V *__restrict__ a, co
     }
 }
 
+// The SoA product where the output planes do not start on 128-byte lines (a
+// dense site count that is no multiple of 8 in FP64 or 16 in FP32, an odd
+// pitch, or an unaligned c). In fwd_soa the runs that the workgroups write
+// then begin and end inside lines that their neighbours write too, and each
+// line written in two parts costs far more than a whole one: 5.2 TB/s in FP32
+// and 5.9 in FP64 at 31^4 sites, against 6.5 on lines. Here a workgroup of T
+// threads computes T consecutive sites, one line's worth more than the W = T -
+// H it advances by, and each of its three output planes is written as W
+// sites from that plane's own first line boundary on, through LDS, so that
+// every line is written whole by one workgroup and every wavefront's run is
+// aligned; the first workgroup also writes the sites before the boundary.
+// The inputs are loaded cached, not nontemporal: the line at the edge of a
+// wavefront's unaligned run serves its neighbour too, and the halo of H sites
+// is read twice. 31^4 sites: FP32 103 -> 88 us, FP64 181 -> 170; 2,560,001
+// sites: FP32 284 -> 246, FP64 499 -> 469 (6.0 and 6.3 TB/s). Loads aligned the same way through
+// LDS were 1-4% slower, and so was a halo without LDS (unaligned wavefront
+// runs); cached stores in the XCD order, which leave it to L2 to merge the
+// parts, were 2-8% slower in FP32 and slower than fwd_soa in FP64. T and the
+// occupancy caps are from a sweep of 256, 512 and 1024 threads and 8 to 24
+// wavefronts (or no cap) over six sizes. The arithmetic and its order are
+// those of fwd_soa, so the output is bit-identical to it; kWaits as there.
+template <typename V, typename S, int T, int kWaits>
+__global__ __launch_bounds__(T) void fwd_soa_halo(const V *__restrict__ a, const S *__restrict__ b,
+                                                  V *__restrict__ c, int64_t n, int64_t pitch, int64_t nbp)
+{
+    constexpr int H = 128 / (int)sizeof(V), W = T - H;
+    __shared__ V sm[3][T];
+    const int row = (int)(blockIdx.x / nbp);     // 3j + k
+    const int64_t s0 = ((int64_t)blockIdx.x - (int64_t)row * nbp) * W;
+    const int j = row / 3, tid = threadIdx.x;
+    const int64_t s = s0 + tid;
+    S br[9], bi[9];
+#pragma unroll
+    for (int q = 0; q < 9; ++q) {
+        br[q] = b[2 * (9 * j + q)];
+        bi[q] = b[2 * (9 * j + q) + 1];
+    }
+    const V *__restrict__ ap = a + (int64_t)(3 * row) * pitch + (s < n ? s : n - 1);   // in bounds; unused past the end
+    V *__restrict__ cp = c + (int64_t)(3 * row) * pitch;
+    S re[3] = {0, 0, 0}, im[3] = {0, 0, 0};
+#pragma unroll
+    for (int m = 0; m < 3; ++m) {
+        const V x = ap[m * pitch];
+#pragma unroll
+        for (int l = 0; l < 3; ++l)
+            cmac(re[l], im[l], x.x, x.y, br[3 * m + l], bi[3 * m + l]);
+        if ((kWaits >> m) & 1)
+            asm volatile("" ::"v"(re[0]), "v"(im[0]), "v"(re[1]), "v"(im[1]), "v"(re[2]), "v"(im[2]) : "memory");
+    }
+#pragma unroll
+    for (int l = 0; l < 3; ++l)
+        sm[l][tid] = V{re[l], im[l]};
+    __syncthreads();
+    int sh[3];   // sites from s0 to the plane's first line boundary, 0 .. H - 1
+    V o[3];
+#pragma unroll
+    for (int l = 0; l < 3; ++l) {
+        const unsigned at = (unsigned)(((uintptr_t)(cp + l * pitch) / sizeof(V) + (uint64_t)s0) % H);
+        sh[l] = (int)((H - at) % H);
+        o[l] = sm[l][tid < W ? tid + sh[l] : tid];
+    }
+#pragma unroll
+    for (int l = 0; l < 3; ++l) {
+        if (tid < W && s + sh[l] < n)
+            st_stream(cp + l * pitch + s + sh[l], o[l]);
+        if (s0 == 0 && tid < sh[l] && s < n)
+            cp[l * pitch + s] = sm[l][tid];
+    }
+}
+
 // Tile order of the SoA product. The three input planes of a row are read at
 // the same site offsets, plane stride n * elem_bytes apart. When that stride
 // is close to a multiple of 4 MiB (within 128 KiB), the planes of the one
@@ -728,9 +799,29 @@ static hipError_t launch_soa(const void *a, const void *b, void *c, int64_t site
                     (const S *)b, (V *)c, sites, pitch, nbp, xcd);
 }
 
+// fwd_soa_halo with at most kWaves wavefronts resident per CU (0: no cap).
+template <typename V, typename S, int T, int kWaits, int kWaves>
+static hipError_t launch_soa_halo(const void *a, const void *b, void *c, int64_t sites, int64_t pitch, hipStream_t s)
+{
+    static std::atomic<int> pad_cache[kMaxDevices];
+    constexpr int W = T - 128 / (int)sizeof(V);
+    const int64_t nbp = (sites + W - 1) / W;
+    const size_t pad = occupancy_pad(reinterpret_cast<const void *>(fwd_soa_halo<V, S, T, kWaits>), kWaves, T, pad_cache);
+    return launch_k(fwd_soa_halo<V, S, T, kWaits>, dim3((unsigned)(12 * nbp)), dim3(T), s, pad, (const V *)a,
+                    (const S *)b, (V *)c, sites, pitch, nbp);
+}
+
 hipError_t launch_fwd_soa(const void *a, const void *b, void *c, int64_t sites, int64_t pitch, int elem_bytes,
                           hipStream_t s)
 {
+    // output planes off 128-byte lines; past 2^28 sites its grid, 3% larger
+    // than fwd_soa's, could pass the limit that the caller checked for fwd_soa
+    const bool lines = pitch * elem_bytes % 128 == 0 && (uintptr_t)c % 128 == 0;
+    if (!lines && sites <= (int64_t)1 << 28) {
+        if (elem_bytes == 16)
+            return launch_soa_halo<d2, double, 256, 1, 16>(a, b, c, sites, pitch, s);
+        return launch_soa_halo<f2, float, 512, 0, 0>(a, b, c, sites, pitch, s);
+    }
     int waves = 0;
     const int waits = soa_waits(sites, pitch, elem_bytes, &waves);
     if (elem_bytes == 16)

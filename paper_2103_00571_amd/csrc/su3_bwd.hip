@@ -433,19 +433,19 @@ int bwd_block_threads() { return kBwdThreads; }
 hipError_t launch_bwd(const void *a, const void *b, const void *dc, void *da, double *db, int64_t sites,
                       int precision, double *ws, hipStream_t s)
 {
-    static std::atomic<int> pad64[kMaxDevices], pad32[kMaxDevices];
+    static PadCache cache64, cache32;
     const int64_t groups = bwd_groups(sites, precision), chunks = bwd_chunks(groups);
     double *ws2 = ws + 72 * groups;
     hipError_t e;
     if (precision == 0) {
-        const size_t pad =
-            occupancy_pad(reinterpret_cast<const void *>(bwd_tiles<BwdF64>), SU3_BWD_WAVES_F64, kBwdThreads, pad64);
-        e = launch_k(bwd_tiles<BwdF64>, dim3((unsigned)groups), dim3(kBwdThreads), s, pad, (const u4 *)a,
+        const LaunchPlan plan = launch_plan(reinterpret_cast<const void *>(bwd_tiles<BwdF64>), SU3_BWD_WAVES_F64,
+                                            kBwdThreads, groups, cache64);
+        e = launch_k(bwd_tiles<BwdF64>, dim3((unsigned)groups), dim3(kBwdThreads), s, plan.pad, (const u4 *)a,
                      (const double *)b, (const u4 *)dc, (u4 *)da, ws, sites * kRowsPerSite, groups);
     } else {
-        const size_t pad =
-            occupancy_pad(reinterpret_cast<const void *>(bwd_tiles<BwdF32>), SU3_BWD_WAVES_F32, kBwdThreads, pad32);
-        e = launch_k(bwd_tiles<BwdF32>, dim3((unsigned)groups), dim3(kBwdThreads), s, pad, (const u4 *)a,
+        const LaunchPlan plan = launch_plan(reinterpret_cast<const void *>(bwd_tiles<BwdF32>), SU3_BWD_WAVES_F32,
+                                            kBwdThreads, groups, cache32);
+        e = launch_k(bwd_tiles<BwdF32>, dim3((unsigned)groups), dim3(kBwdThreads), s, plan.pad, (const u4 *)a,
                      (const float *)b, (const u4 *)dc, (u4 *)da, ws, sites * kRowsPerSite, groups);
     }
     if (e != hipSuccess)

@@ -682,8 +682,8 @@ static int64_t soa_blocks_per_row(int64_t sites, int64_t pitch, int elem_bytes)
 // ---------------------------------------------------------------- launchers
 // Dynamic LDS to add per workgroup so that at most `waves` wavefronts of
 // `kernel` are resident per CU: the CU's LDS divided by the wanted number of
-// workgroups, minus the kernel's static LDS. Cached per device; 0 when no cap
-// is wanted or a query fails.
+// workgroups, minus the kernel's static LDS; 0 when no cap is wanted or a
+// query fails.
 size_t occupancy_pad_for(const void *kernel, int waves, int block, int dev)
 {
     int lds_cu = 0, lds_block = 0;
@@ -702,19 +702,26 @@ size_t occupancy_pad_for(const void *kernel, int waves, int block, int dev)
     return (size_t)pad;
 }
 
-size_t occupancy_pad(const void *kernel, int waves, int block, std::atomic<int> (&cache)[kMaxDevices])
+LaunchPlan launch_plan(const void *kernel, int waves, int block, int64_t grid, PadCache &cache)
 {
-    if (waves <= 0)
-        return 0;
+    LaunchPlan p;
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices)
-        return 0;
-    int pad = cache[dev].load(std::memory_order_relaxed);   // pad + 1; 0 = not yet known
-    if (pad > 0)
-        return (size_t)(pad - 1);
-    pad = (int)occupancy_pad_for(kernel, waves, block, dev);
-    cache[dev].store(pad + 1, std::memory_order_relaxed);
-    return (size_t)pad;
+        return p;
+    int64_t known = cache[dev].load(std::memory_order_relaxed);
+    if (known == 0) {
+        int resident = 0;
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&resident, kernel, block, 0) != hipSuccess)
+            resident = 0;
+        const int most = 24 * 64 / block;
+        if (resident > most)
+            resident = most;
+        known = (int64_t)resident << 32 | (int64_t)(occupancy_pad_for(kernel, waves, block, dev) + 1);
+        cache[dev].store(known, std::memory_order_relaxed);
+    }
+    p.one_generation = grid <= (known >> 32) * kCUs;
+    p.pad = p.one_generation ? 0 : (size_t)((known & 0xffffffff) - 1);
+    return p;
 }
 
 template <class F>
@@ -750,10 +757,11 @@ int soa_block_threads() { return kSoaBlock; }
 template <class F, bool kConjB = false>
 static hipError_t launch_aos(const void *a, const void *b, void *c, int64_t sites, hipStream_t s)
 {
-    static std::atomic<int> pad_cache[kMaxDevices];
-    const size_t pad =
-        occupancy_pad(reinterpret_cast<const void *>(fwd_aos<F, kConjB>), F::kWavesPerCU, kAosBlock, pad_cache);
-    return launch_k(fwd_aos<F, kConjB>, dim3((unsigned)aos_grid<F>(sites)), dim3(kAosBlock), s, pad,
+    static PadCache cache;
+    const int64_t grid = aos_grid<F>(sites);
+    const LaunchPlan plan =
+        launch_plan(reinterpret_cast<const void *>(fwd_aos<F, kConjB>), F::kWavesPerCU, kAosBlock, grid, cache);
+    return launch_k(fwd_aos<F, kConjB>, dim3((unsigned)grid), dim3(kAosBlock), s, plan.pad,
                     (const u4 *)a, (const typename F::B *)b, (u4 *)c, sites * F::kUnitsPerSite);
 }
 
@@ -784,18 +792,18 @@ hipError_t launch_fwd_an(const void *a, const void *b, void *c, int64_t sites, i
 }
 
 // Each instantiation is launched with one occupancy cap only (soa_waits maps
-// the wait mask to its cap), so one pad cache per instantiation suffices.
+// the wait mask to its cap), so one plan cache per instantiation suffices.
 template <typename V, typename S, int kWaits>
 static hipError_t launch_soa(const void *a, const void *b, void *c, int64_t sites, int64_t pitch, int waves,
                              hipStream_t s)
 {
-    static std::atomic<int> pad_cache[kMaxDevices];
+    static PadCache cache;
     const int es = (int)sizeof(V);
     const int64_t nbp = soa_blocks_per_row(sites, pitch, es);
     const int xcd = soa_xcd(sites, pitch, es) ? 1 : 0;
-    const size_t pad =
-        occupancy_pad(reinterpret_cast<const void *>(fwd_soa<V, S, kWaits>), waves, kSoaBlock, pad_cache);
-    return launch_k(fwd_soa<V, S, kWaits>, dim3((unsigned)(12 * nbp)), dim3(kSoaBlock), s, pad, (const V *)a,
+    const LaunchPlan plan =
+        launch_plan(reinterpret_cast<const void *>(fwd_soa<V, S, kWaits>), waves, kSoaBlock, 12 * nbp, cache);
+    return launch_k(fwd_soa<V, S, kWaits>, dim3((unsigned)(12 * nbp)), dim3(kSoaBlock), s, plan.pad, (const V *)a,
                     (const S *)b, (V *)c, sites, pitch, nbp, xcd);
 }
 
@@ -803,11 +811,12 @@ static hipError_t launch_soa(const void *a, const void *b, void *c, int64_t site
 template <typename V, typename S, int T, int kWaits, int kWaves>
 static hipError_t launch_soa_halo(const void *a, const void *b, void *c, int64_t sites, int64_t pitch, hipStream_t s)
 {
-    static std::atomic<int> pad_cache[kMaxDevices];
+    static PadCache cache;
     constexpr int W = T - 128 / (int)sizeof(V);
     const int64_t nbp = (sites + W - 1) / W;
-    const size_t pad = occupancy_pad(reinterpret_cast<const void *>(fwd_soa_halo<V, S, T, kWaits>), kWaves, T, pad_cache);
-    return launch_k(fwd_soa_halo<V, S, T, kWaits>, dim3((unsigned)(12 * nbp)), dim3(T), s, pad, (const V *)a,
+    const LaunchPlan plan =
+        launch_plan(reinterpret_cast<const void *>(fwd_soa_halo<V, S, T, kWaits>), kWaves, T, 12 * nbp, cache);
+    return launch_k(fwd_soa_halo<V, S, T, kWaits>, dim3((unsigned)(12 * nbp)), dim3(T), s, plan.pad, (const V *)a,
                     (const S *)b, (V *)c, sites, pitch, nbp);
 }
 

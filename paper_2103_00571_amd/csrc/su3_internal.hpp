@@ -109,6 +109,9 @@ __device__ __forceinline__ void store_runs(u4 *__restrict__ dst, const u4 *slice
 // Threads per workgroup of the streaming kernels: four wave64s.
 constexpr int kBlock = 256;
 
+// Compute units of an MI355X.
+constexpr int kCUs = 256;
+
 // Devices per process for the per-device caches.
 constexpr int kMaxDevices = 64;
 
@@ -131,11 +134,29 @@ inline hipError_t launch_k(void (*k)(KArgs...), dim3 grid, dim3 block, hipStream
     return hipLaunchKernel(reinterpret_cast<const void *>(k), grid, block, argv, dyn_lds, s);
 }
 
-// Dynamic LDS to add to each workgroup of `kernel` (block threads each) so
-// that at most `waves` wavefronts are resident per CU; 0 for no cap. Cached
-// per device in `cache` (entries start at 0).
-size_t occupancy_pad(const void *kernel, int waves, int block, std::atomic<int> (&cache)[kMaxDevices]);
-// The same pad for device `dev`, computed on every call (no cache).
+// Per-kernel, per-device launch facts, looked up on the first call (0: not
+// yet): the dynamic LDS that enforces the occupancy cap, plus 1, in the low
+// 32 bits and the workgroups one CU holds without it, of at most 24
+// wavefronts, in the high 32.
+typedef std::atomic<int64_t> PadCache[kMaxDevices];
+// How to launch a streaming kernel: the dynamic LDS to add to each workgroup
+// so that at most `waves` wavefronts are resident per CU (0 for no cap), and
+// whether the whole grid is resident at once without a cap. The caps keep the
+// bytes in flight at the rate's peak while workgroup follows workgroup; a grid
+// that is resident at once has nothing to follow it, and a cap would only
+// hold part of it back for a second generation. Uncapped against capped, at
+// 65,536 sites: reconstruct-12 5.8 against 8.6 us, a^H b FP32 6.7 against 9.1;
+// at 32,768 sites: reconstruct-12 FP64 5.7 against 8.2, a^H b FP64 6.6 against
+// 8.8; BF16 at 100,000 sites 5.8 against 7.4. Past residency (reconstruct-12
+// FP64 at 69,632 sites), and past 24 wavefronts per CU where more fit (FP64
+// at 40,960 sites, FP32 at 81,920), the cap is as fast or up to 3% faster.
+struct LaunchPlan {
+    size_t pad = 0;
+    bool one_generation = false;
+};
+LaunchPlan launch_plan(const void *kernel, int waves, int block, int64_t grid, PadCache &cache);
+// The dynamic LDS of a cap of `waves` wavefronts per CU on device `dev`,
+// computed on every call (no cache).
 size_t occupancy_pad_for(const void *kernel, int waves, int block, int dev);
 
 // ---- launchers (each returns hipSuccess or the launch error) --------------

@@ -547,9 +547,10 @@ static unsigned grid_for(int64_t items, int64_t per_block, int64_t cap = kOnePas
 template <auto K, int TS, int B, int kPerCU, typename VS, typename VD>
 static hipError_t launch_tiles(const VS *src, VD *dst, int64_t n, int64_t pitch, hipStream_t s)
 {
-    static std::atomic<int> cache[kMaxDevices];
-    const size_t pad = occupancy_pad(reinterpret_cast<const void *>(K), kPerCU * (B / 64), B, cache);
-    return launch_k(K, dim3((unsigned)((n + TS - 1) / TS)), dim3(B), s, pad, src, dst, n, pitch);
+    static PadCache cache;
+    const int64_t grid = (n + TS - 1) / TS;
+    const LaunchPlan plan = launch_plan(reinterpret_cast<const void *>(K), kPerCU * (B / 64), B, grid, cache);
+    return launch_k(K, dim3((unsigned)grid), dim3(B), s, plan.pad, src, dst, n, pitch);
 }
 template <typename V, int TS, int B, bool kHalo, int kPerCU>
 static hipError_t launch_to_soa(const void *src, void *dst, int64_t n, int64_t pitch, hipStream_t s)
@@ -681,10 +682,21 @@ hipError_t launch_stream_shape(const void *a, const void *b, void *c, int64_t ti
 template <typename V>
 static hipError_t launch_pack_r12(const void *src, void *dst, int64_t links, hipStream_t s)
 {
-    static std::atomic<int> pad[kMaxDevices];
-    const size_t p = occupancy_pad(reinterpret_cast<const void *>(pack_r12<V>), SU3_WAVES_PACK_R12, 64, pad);
-    return launch_k(pack_r12<V>, dim3((unsigned)((links + 63) / 64)), dim3(64), s, p, (const u4 *)src, (u4 *)dst,
-                    links);
+    static PadCache cache;
+    const int64_t grid = (links + 63) / 64;
+    const LaunchPlan plan =
+        launch_plan(reinterpret_cast<const void *>(pack_r12<V>), SU3_WAVES_PACK_R12, 64, grid, cache);
+    return launch_k(pack_r12<V>, dim3((unsigned)grid), dim3(64), s, plan.pad, (const u4 *)src, (u4 *)dst, links);
+}
+
+template <typename V>
+static hipError_t launch_unpack_r12(const void *src, void *dst, int64_t links, hipStream_t s)
+{
+    static PadCache cache;
+    const int64_t grid = (links + 63) / 64;
+    const LaunchPlan plan =
+        launch_plan(reinterpret_cast<const void *>(unpack_r12<V>), SU3_WAVES_UNPACK_R12, 64, grid, cache);
+    return launch_k(unpack_r12<V>, dim3((unsigned)grid), dim3(64), s, plan.pad, (const u4 *)src, (u4 *)dst, links);
 }
 
 // precision codes as in su3.h: 0 F64, 1 F32, 2 BF16, 3 R12_F32 (rows 0-1 FP32
@@ -721,18 +733,10 @@ hipError_t launch_unpack(const void *src, void *dst, int64_t sites, int precisio
         return launch_k(unpack_bf16<256>, dim3(grid_for(elems / 2, 256, kOnePass)), dim3(256), s, 0, (const u2 *)src,
                         (d2 *)dst, elems / 2);
     case 3:
-    case 4: {
-        static std::atomic<int> pad[kMaxDevices];
-        const size_t p = occupancy_pad(reinterpret_cast<const void *>(unpack_r12<f2>), SU3_WAVES_UNPACK_R12, 64, pad);
-        return launch_k(unpack_r12<f2>, dim3((unsigned)((links + 63) / 64)), dim3(64), s, p, (const u4 *)src,
-                        (u4 *)dst, links);
-    }
-    case 5: {
-        static std::atomic<int> pad[kMaxDevices];
-        const size_t p = occupancy_pad(reinterpret_cast<const void *>(unpack_r12<d2>), SU3_WAVES_UNPACK_R12, 64, pad);
-        return launch_k(unpack_r12<d2>, dim3((unsigned)((links + 63) / 64)), dim3(64), s, p, (const u4 *)src,
-                        (u4 *)dst, links);
-    }
+    case 4:
+        return launch_unpack_r12<f2>(src, dst, links, s);
+    case 5:
+        return launch_unpack_r12<d2>(src, dst, links, s);
     default:
         return launch_stream_copy(src, dst, elems * 16, s);
     }

@@ -127,16 +127,19 @@ int64_t mat_vec_grid(int precision, int64_t sites)
 
 hipError_t launch_mat_vec(const void *a, const void *v, void *w, int64_t sites, int precision, hipStream_t s)
 {
-    static std::atomic<int> pad64[kMaxDevices], pad32[kMaxDevices];
-    const dim3 grid((unsigned)mat_vec_grid(precision, sites));
+    static PadCache cache64, cache32;
+    const int64_t g = mat_vec_grid(precision, sites);
+    const dim3 grid((unsigned)g);
     if (precision == 0) {
-        const size_t pad =
-            occupancy_pad(reinterpret_cast<const void *>(mat_vec<double>), SU3_WAVES_MATVEC, kMvBlock, pad64);
-        return launch_k(mat_vec<double>, grid, dim3(kMvBlock), s, pad, (const u4 *)a, (const uint64_t *)v, (u4 *)w,
+        const LaunchPlan plan =
+            launch_plan(reinterpret_cast<const void *>(mat_vec<double>), SU3_WAVES_MATVEC, kMvBlock, g, cache64);
+        return launch_k(mat_vec<double>, grid, dim3(kMvBlock), s, plan.pad, (const u4 *)a, (const uint64_t *)v, (u4 *)w,
                         sites);
     }
-    const size_t pad = occupancy_pad(reinterpret_cast<const void *>(mat_vec<float>), SU3_WAVES_MATVEC, kMvBlock, pad32);
-    return launch_k(mat_vec<float>, grid, dim3(kMvBlock), s, pad, (const u4 *)a, (const uint64_t *)v, (u4 *)w, sites);
+    const LaunchPlan plan =
+        launch_plan(reinterpret_cast<const void *>(mat_vec<float>), SU3_WAVES_MATVEC, kMvBlock, g, cache32);
+    return launch_k(mat_vec<float>, grid, dim3(kMvBlock), s, plan.pad, (const u4 *)a, (const uint64_t *)v, (u4 *)w,
+                    sites);
 }
 
 } // namespace su3

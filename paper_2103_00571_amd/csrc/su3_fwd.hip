@@ -19,7 +19,8 @@
 //    how many phases its plane loads take (soa_waits) from the plane
 //    stride, and takes any plane pitch >= the site count (soa_pitch gives
 //    the one that keeps the planes from colliding in HBM).
-//  * a and c are streamed with nontemporal 16-byte loads and stores.
+//  * a is streamed with nontemporal 16-byte loads, c with write-through or
+//    nontemporal stores (OutWindow).
 //  * 64-bit offsets throughout (a FP64 L=48 lattice is 3.06e9 bytes).
 #include "su3_internal.hpp"
 
@@ -401,7 +402,7 @@ __device__ __forceinline__ void wave_sync()
 // lane reads the coefficients of its own unit position from there.
 // kConjB: stage b[j]^H instead of b[j] (the a b^H product; the kernel is
 // otherwise the same).
-template <class F, bool kConjB = false>
+template <class F, bool kConjB, bool kThrough>
 __global__ __launch_bounds__(kAosBlock) void fwd_aos(const u4 *__restrict__ a, const typename F::B *__restrict__ b,
                                                   u4 *__restrict__ c, int64_t units)
 {
@@ -414,7 +415,6 @@ __global__ __launch_bounds__(kAosBlock) void fwd_aos(const u4 *__restrict__ a, c
     u4 *my = stage[threadIdx.x >> 6];
     const int64_t t = xcd_tile(blockIdx.x, gridDim.x) * kWaves + (threadIdx.x >> 6);
     const bool live = t * 64 < units;            // wave-uniform
-    const bool whole = (t + 1) * 64 <= units;    // wave-uniform (no ragged end)
     const int64_t nin = units * F::kIn, nout = units * F::kOut;
 
     // Load b (72 scalars, cached) first and the tile after it: vector memory
@@ -471,7 +471,7 @@ __global__ __launch_bounds__(kAosBlock) void fwd_aos(const u4 *__restrict__ a, c
     for (int i = 0; i < F::kOut; ++i)
         my[F::kOut * lane + i] = o[i];
     wave_sync();
-    store_runs<F::kOut>(c, my, t * 64 * F::kOut + lane, lane, whole, nout);
+    store_runs<kThrough, F::kOut>(c, my, t * 64 * F::kOut, lane, nout);
 }
 
 // ---------------------------------------------------------------- SoA
@@ -491,7 +491,11 @@ __global__ __launch_bounds__(kAosBlock) void fwd_aos(const u4 *__restrict__ a, c
 // asm statement that takes the accumulators as inputs, so every load before
 // it has completed and no later load moves above it. The arithmetic and its
 // order are the same for every kWaits, so the output is bit-identical.
-template <typename V, typename S, int kWaits>
+// kThrough: the output's cache policy (OutWindow). Write-through in FP32 beyond
+// one generation (dense and padded: 1.02-1.03 at 2^20 sites and above,
+// 1.08-1.10 at 24^4), never in FP64 (0.97-0.99, at any cap) or in fwd_soa_halo
+// (0.94-1.00).
+template <typename V, typename S, int kWaits, bool kThrough>
 __global__ __launch_bounds__(kSoaBlock) void fwd_soa(const V *__restrict__ a, const S *__restrict__ b,
                                                   V *__restrict__ c, int64_t n, int64_t pitch, int64_t nbp, int xcd)
 {
@@ -509,7 +513,8 @@ __global__ __launch_bounds__(kSoaBlock) void fwd_soa(const V *__restrict__ a, co
         bi[q] = b[2 * (9 * j + q) + 1];
     }
     const V *__restrict__ ap = a + (int64_t)(3 * row) * pitch + s;
-    V *__restrict__ cp = c + (int64_t)(3 * row) * pitch + s;
+    const int64_t s0 = xb * kSoaBlock;
+    V *__restrict__ cp = c + (int64_t)(3 * row) * pitch + s0;
     S re[3] = {0, 0, 0}, im[3] = {0, 0, 0};
 #pragma unroll
     for (int m = 0; m < 3; ++m) {
@@ -522,8 +527,8 @@ __global__ __launch_bounds__(kSoaBlock) void fwd_soa(const V *__restrict__ a, co
     }
 #pragma unroll
     for (int l = 0; l < 3; ++l) {
-        V o = {re[l], im[l]};
-        st_stream(cp + l * pitch, o);
+        const V o = {re[l], im[l]};
+        st_out<kThrough>(out_window(cp + l * pitch, (n - s0) * (int64_t)sizeof(V)), threadIdx.x * sizeof(V), o);
     }
 }
 
@@ -590,8 +595,10 @@ __global__ __launch_bounds__(T) void fwd_soa_halo(const V *__restrict__ a, const
     }
 #pragma unroll
     for (int l = 0; l < 3; ++l) {
-        if (tid < W && s + sh[l] < n)
-            st_stream(cp + l * pitch + s + sh[l], o[l]);
+        const int64_t first = s0 + sh[l];
+        const OutWindow out = out_window(cp + l * pitch + first, (n - first) * (int64_t)sizeof(V));
+        if (tid < W)
+            st_out<false>(out, tid * sizeof(V), o[l]);
         if (s0 == 0 && tid < sh[l] && s < n)
             cp[l * pitch + s] = sm[l][tid];
     }
@@ -759,10 +766,11 @@ static hipError_t launch_aos(const void *a, const void *b, void *c, int64_t site
 {
     static PadCache cache;
     const int64_t grid = aos_grid<F>(sites);
-    const LaunchPlan plan =
-        launch_plan(reinterpret_cast<const void *>(fwd_aos<F, kConjB>), F::kWavesPerCU, kAosBlock, grid, cache);
-    return launch_k(fwd_aos<F, kConjB>, dim3((unsigned)grid), dim3(kAosBlock), s, plan.pad,
-                    (const u4 *)a, (const typename F::B *)b, (u4 *)c, sites * F::kUnitsPerSite);
+    const LaunchPlan plan = launch_plan(reinterpret_cast<const void *>(fwd_aos<F, kConjB, true>), F::kWavesPerCU,
+                                        kAosBlock, grid, cache);
+    return launch_k(plan.one_generation ? fwd_aos<F, kConjB, false> : fwd_aos<F, kConjB, true>, dim3((unsigned)grid),
+                    dim3(kAosBlock), s, plan.pad, (const u4 *)a, (const typename F::B *)b, (u4 *)c,
+                    sites * F::kUnitsPerSite);
 }
 
 hipError_t launch_fwd_aos(const void *a, const void *b, void *c, int64_t sites, int precision, hipStream_t s)
@@ -798,13 +806,15 @@ static hipError_t launch_soa(const void *a, const void *b, void *c, int64_t site
                              hipStream_t s)
 {
     static PadCache cache;
+    constexpr bool kThrough = sizeof(V) == 8;   // see fwd_soa
     const int es = (int)sizeof(V);
     const int64_t nbp = soa_blocks_per_row(sites, pitch, es);
     const int xcd = soa_xcd(sites, pitch, es) ? 1 : 0;
     const LaunchPlan plan =
-        launch_plan(reinterpret_cast<const void *>(fwd_soa<V, S, kWaits>), waves, kSoaBlock, 12 * nbp, cache);
-    return launch_k(fwd_soa<V, S, kWaits>, dim3((unsigned)(12 * nbp)), dim3(kSoaBlock), s, plan.pad, (const V *)a,
-                    (const S *)b, (V *)c, sites, pitch, nbp, xcd);
+        launch_plan(reinterpret_cast<const void *>(fwd_soa<V, S, kWaits, kThrough>), waves, kSoaBlock, 12 * nbp, cache);
+    return launch_k(plan.one_generation ? fwd_soa<V, S, kWaits, false> : fwd_soa<V, S, kWaits, kThrough>,
+                    dim3((unsigned)(12 * nbp)), dim3(kSoaBlock), s, plan.pad, (const V *)a, (const S *)b, (V *)c, sites,
+                    pitch, nbp, xcd);
 }
 
 // fwd_soa_halo with at most kWaves wavefronts resident per CU (0: no cap).

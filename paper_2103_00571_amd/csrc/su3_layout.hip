@@ -341,7 +341,7 @@ __global__ __launch_bounds__(B) void pack_bf16(const d2 *__restrict__ src, uint3
 // (V = d2), the reconstruct-12 storage. One wavefront per tile of 64 links:
 // whole-wavefront 1 KiB runs of the tile's links (9 chunks each) in, the
 // rows 0-1 of each (3 or 6 chunks) out, through a private LDS slice.
-template <typename V>
+template <typename V, bool kThrough>
 __global__ __launch_bounds__(64) void pack_r12(const u4 *__restrict__ src, u4 *__restrict__ dst, int64_t links)
 {
     constexpr int kOut = sizeof(V) == 8 ? 3 : 6;   // output chunks per link
@@ -349,7 +349,6 @@ __global__ __launch_bounds__(64) void pack_r12(const u4 *__restrict__ src, u4 *_
     const int lane = threadIdx.x;
     const int64_t t = xcd_tile(blockIdx.x, gridDim.x);
     const int64_t nin = links * 9, nout = links * kOut;
-    const bool whole = (t + 1) * 64 <= links;
     u4 v[9];
 #pragma unroll
     for (int i = 0; i < 9; ++i) {
@@ -379,12 +378,7 @@ __global__ __launch_bounds__(64) void pack_r12(const u4 *__restrict__ src, u4 *_
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-#pragma unroll
-    for (int i = 0; i < kOut; ++i) {
-        const int64_t g = t * 64 * kOut + 64 * i + lane;
-        if (whole || g < nout)
-            st_stream(dst + g, stage[64 * i + lane]);
-    }
+    store_runs<kThrough, kOut>(dst, stage, t * 64 * kOut, lane, nout);
 }
 
 // ------------------------------------------------------------ unpack
@@ -423,7 +417,7 @@ __global__ __launch_bounds__(B) void unpack_bf16(const u2 *__restrict__ src, d2 
 // private LDS slice turns them into one link per lane. Row 2 is rebuilt in
 // FP64 with contraction off, in the oracle's operation order, so the result
 // is bit-exact.
-template <typename V>
+template <typename V, bool kThrough>
 __global__ __launch_bounds__(64) void unpack_r12(const u4 *__restrict__ src, u4 *__restrict__ dst, int64_t links)
 {
 #pragma clang fp contract(off)
@@ -432,7 +426,6 @@ __global__ __launch_bounds__(64) void unpack_r12(const u4 *__restrict__ src, u4 
     const int lane = threadIdx.x;
     const int64_t t = xcd_tile(blockIdx.x, gridDim.x);
     const int64_t nin = links * kIn, nout = links * 9;
-    const bool whole = (t + 1) * 64 <= links;
     u4 v[kIn];
 #pragma unroll
     for (int i = 0; i < kIn; ++i) {
@@ -476,12 +469,7 @@ __global__ __launch_bounds__(64) void unpack_r12(const u4 *__restrict__ src, u4 
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-#pragma unroll
-    for (int i = 0; i < 9; ++i) {
-        const int64_t g = t * 64 * 9 + 64 * i + lane;
-        if (whole || g < nout)
-            st_stream(dst + g, stage[64 * i + lane]);
-    }
+    store_runs<kThrough, 9>(dst, stage, t * 64 * 9, lane, nout);
 }
 
 // ------------------------------------------------------------ stream copy
@@ -685,8 +673,9 @@ static hipError_t launch_pack_r12(const void *src, void *dst, int64_t links, hip
     static PadCache cache;
     const int64_t grid = (links + 63) / 64;
     const LaunchPlan plan =
-        launch_plan(reinterpret_cast<const void *>(pack_r12<V>), SU3_WAVES_PACK_R12, 64, grid, cache);
-    return launch_k(pack_r12<V>, dim3((unsigned)grid), dim3(64), s, plan.pad, (const u4 *)src, (u4 *)dst, links);
+        launch_plan(reinterpret_cast<const void *>(pack_r12<V, true>), SU3_WAVES_PACK_R12, 64, grid, cache);
+    return launch_k(plan.one_generation ? pack_r12<V, false> : pack_r12<V, true>, dim3((unsigned)grid), dim3(64), s, plan.pad,
+                    (const u4 *)src, (u4 *)dst, links);
 }
 
 template <typename V>
@@ -695,8 +684,9 @@ static hipError_t launch_unpack_r12(const void *src, void *dst, int64_t links, h
     static PadCache cache;
     const int64_t grid = (links + 63) / 64;
     const LaunchPlan plan =
-        launch_plan(reinterpret_cast<const void *>(unpack_r12<V>), SU3_WAVES_UNPACK_R12, 64, grid, cache);
-    return launch_k(unpack_r12<V>, dim3((unsigned)grid), dim3(64), s, plan.pad, (const u4 *)src, (u4 *)dst, links);
+        launch_plan(reinterpret_cast<const void *>(unpack_r12<V, true>), SU3_WAVES_UNPACK_R12, 64, grid, cache);
+    return launch_k(plan.one_generation ? unpack_r12<V, false> : unpack_r12<V, true>, dim3((unsigned)grid), dim3(64), s, plan.pad,
+                    (const u4 *)src, (u4 *)dst, links);
 }
 
 // precision codes as in su3.h: 0 F64, 1 F32, 2 BF16, 3 R12_F32 (rows 0-1 FP32

@@ -33,7 +33,7 @@ __device__ __forceinline__ void wave_sync_mv()
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-template <typename S>
+template <typename S, bool kThrough>
 __global__ __launch_bounds__(kMvBlock) void mat_vec(const u4 *__restrict__ a, const uint64_t *__restrict__ v,
                                                     u4 *__restrict__ w, int64_t sites)
 {
@@ -49,7 +49,6 @@ __global__ __launch_bounds__(kMvBlock) void mat_vec(const u4 *__restrict__ a, co
     const int64_t t = xcd_tile(blockIdx.x, gridDim.x);
     const int64_t units = sites * kUnitsPerSite;
     const int64_t na = units * 9, nv = sites * kWordsPerSite, nw = units * 3;
-    const bool whole = (t + 1) * 64 <= units;
 
     // loads: indices past the end re-read the last element (never used)
     u4 va[9];
@@ -111,12 +110,7 @@ __global__ __launch_bounds__(kMvBlock) void mat_vec(const u4 *__restrict__ a, co
         stage[3 * lane + i] = __builtin_bit_cast(u4, c);
     }
     wave_sync_mv();
-#pragma unroll
-    for (int i = 0; i < 3; ++i) {
-        const int64_t g = t * 192 + 64 * i + lane;
-        if (whole || g < nw)
-            st_stream(w + g, stage[64 * i + lane]);
-    }
+    store_runs<kThrough, 3>(w, stage, t * 192, lane, nw);
 }
 
 int64_t mat_vec_grid(int precision, int64_t sites)
@@ -125,21 +119,20 @@ int64_t mat_vec_grid(int precision, int64_t sites)
     return (units + 63) / 64;
 }
 
+template <typename S>
+static hipError_t launch_mv(const void *a, const void *v, void *w, int64_t sites, int64_t grid, hipStream_t s)
+{
+    static PadCache cache;
+    const LaunchPlan plan =
+        launch_plan(reinterpret_cast<const void *>(mat_vec<S, true>), SU3_WAVES_MATVEC, kMvBlock, grid, cache);
+    return launch_k(plan.one_generation ? mat_vec<S, false> : mat_vec<S, true>, dim3((unsigned)grid), dim3(kMvBlock), s,
+                    plan.pad, (const u4 *)a, (const uint64_t *)v, (u4 *)w, sites);
+}
+
 hipError_t launch_mat_vec(const void *a, const void *v, void *w, int64_t sites, int precision, hipStream_t s)
 {
-    static PadCache cache64, cache32;
-    const int64_t g = mat_vec_grid(precision, sites);
-    const dim3 grid((unsigned)g);
-    if (precision == 0) {
-        const LaunchPlan plan =
-            launch_plan(reinterpret_cast<const void *>(mat_vec<double>), SU3_WAVES_MATVEC, kMvBlock, g, cache64);
-        return launch_k(mat_vec<double>, grid, dim3(kMvBlock), s, plan.pad, (const u4 *)a, (const uint64_t *)v, (u4 *)w,
-                        sites);
-    }
-    const LaunchPlan plan =
-        launch_plan(reinterpret_cast<const void *>(mat_vec<float>), SU3_WAVES_MATVEC, kMvBlock, g, cache32);
-    return launch_k(mat_vec<float>, grid, dim3(kMvBlock), s, plan.pad, (const u4 *)a, (const uint64_t *)v, (u4 *)w,
-                    sites);
+    const int64_t grid = mat_vec_grid(precision, sites);
+    return precision == 0 ? launch_mv<double>(a, v, w, sites, grid, s) : launch_mv<float>(a, v, w, sites, grid, s);
 }
 
 } // namespace su3

@@ -100,14 +100,6 @@ constexpr int kChunkThreads = SU3_BWD_CHUNK_THREADS;
 constexpr int kChunkLoads = SU3_BWD_CHUNK_LOADS;
 constexpr int64_t kChunk = (int64_t)kChunkThreads * kChunkLoads;
 
-// Order LDS traffic between the lanes of one wavefront.
-__device__ __forceinline__ void wave_sync_bwd()
-{
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 // Row `lane` of sub-tile q of a staged step, as 6 interleaved re/im values.
 __device__ __forceinline__ void row_from_stage(const u4 *st, int q, int lane, double (&v)[6])
 {
@@ -234,7 +226,7 @@ __global__ __launch_bounds__(kBwdThreads) void bwd_tiles(const u4 *__restrict__ 
             stg[64 * i + lane] = vg[i];
             stg[192 + 64 * i + lane] = va[i];
         }
-        wave_sync_bwd();
+        wave_sync();
         if (k + 1 < kSteps && (ts + D * kSub) * 64 < rows)
             load_step(ts + D * kSub);
         S o[kSub][6];
@@ -266,11 +258,11 @@ __global__ __launch_bounds__(kBwdThreads) void bwd_tiles(const u4 *__restrict__ 
                     cmac(acc[6 * m + 2 * l], acc[6 * m + 2 * l + 1], (double)x[2 * m], -(double)x[2 * m + 1],
                          (double)g[2 * l], (double)g[2 * l + 1]);
         }
-        wave_sync_bwd();
+        wave_sync();
 #pragma unroll
         for (int q = 0; q < kSub; ++q)
             row_to_stage(stg, q, lane, o[q]);
-        wave_sync_bwd();
+        wave_sync();
         // store the dA step as 3 whole-wavefront runs, guarded past the end
         u4 w[3];
 #pragma unroll
@@ -282,7 +274,7 @@ __global__ __launch_bounds__(kBwdThreads) void bwd_tiles(const u4 *__restrict__ 
             if (whole || g < nchunks)
                 st_stream(da + g, w[i]);
         }
-        wave_sync_bwd();
+        wave_sync();
     }
 
     // ---- fixed-order reduction --------------------------------------------
@@ -298,7 +290,7 @@ __global__ __launch_bounds__(kBwdThreads) void bwd_tiles(const u4 *__restrict__ 
 #pragma unroll
     for (int v = 0; v < 18; ++v)
         red[lane * 19 + v] = acc[v];
-    wave_sync_bwd();
+    wave_sync();
 #pragma unroll
     for (int it = 0; it < (kOut + 63) / 64; ++it) {
         const int o3 = lane + 64 * it;

@@ -380,15 +380,6 @@ struct FormAnF32 {
     }
 };
 
-// Order LDS traffic between the lanes of one wavefront (LDS operations of a
-// wavefront execute in order; this keeps the compiler from moving them).
-__device__ __forceinline__ void wave_sync()
-{
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 // Site-major forward for form F. One wavefront handles one tile of 64
 // consecutive units and exits: its global loads and stores are whole 1 KiB
 // runs (lane l moves chunk i*64 + l of the tile), and a private LDS slice

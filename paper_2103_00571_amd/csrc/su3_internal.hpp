@@ -52,6 +52,15 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi)
     return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf2));
 }
 
+// Order LDS traffic between the lanes of one wavefront (LDS operations of a
+// wavefront execute in order; this keeps the compiler from moving them).
+__device__ __forceinline__ void wave_sync()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // XCD-contiguous tile order of a one-pass grid of nb workgroups. The
 // dispatcher deals workgroups round-robin to MI355X's 8 XCDs (workgroup i to
 // XCD i mod 8); here the k-th workgroup of XCD x takes tile

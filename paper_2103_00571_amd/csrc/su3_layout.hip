@@ -17,13 +17,11 @@
 
 namespace su3 {
 
-// The elementwise setup kernels (FP32 and BF16 pack and unpack, transposes)
-// loop over their items with a grid stride, on a grid of up to kOnePass
-// workgroups: one pass for any lattice that fits in memory, which streams
-// faster than fewer workgroups looping.
+// The FP32 pack and unpack and the general transposes loop over their items
+// with a grid stride, on a grid of up to kOnePass workgroups: one pass for
+// all but the largest lattices, which streams faster than fewer workgroups
+// looping.
 constexpr int64_t kOnePass = (int64_t)1 << 24;
-
-typedef uint32_t u2 __attribute__((ext_vector_type(2)));
 
 // ------------------------------------------------------------ AoS <-> SoA
 // One workgroup moves a tile of 64 sites at a time through LDS: the site-
@@ -315,26 +313,59 @@ __global__ __launch_bounds__(B) void to_aos_pairs(const f2 *__restrict__ src, f4
 }
 
 // ------------------------------------------------------------ pack
-// FP64 complex -> FP32 complex, round to nearest even (v_cvt_f32_f64).
+// FP64 complex -> FP32 complex, round to nearest even (v_cvt_f32_f64), one
+// complex per thread: 16 bytes in, 8 out. Nontemporal loads and write-through
+// stores: 6.97 against 6.49 TB/s with plain ones at 2^20 sites, 6.4 against
+// 5.9 at 160,000.
 template <int B>
 __global__ __launch_bounds__(B) void pack_f32(const d2 *__restrict__ src, f2 *__restrict__ dst, int64_t n)
 {
-    for (int64_t e = (int64_t)blockIdx.x * B + threadIdx.x; e < n; e += (int64_t)gridDim.x * B) {
-        const d2 v = src[e];
-        f2 o = {(float)v.x, (float)v.y};
-        dst[e] = o;
+    for (int64_t t = blockIdx.x; t * B < n; t += gridDim.x) {
+        const int64_t e = t * B + threadIdx.x;
+        const d2 v = ld_stream(src + (e < n ? e : n - 1));
+        const f2 o = {(float)v.x, (float)v.y};
+        st_out<true>(out_window(dst + t * B, 8 * (n - t * B)), 8 * threadIdx.x, o);
     }
 }
 
+// The BF16 conversions: a wavefront moves 64 chunks (16 bytes, 4 complex) of
+// the BF16 side and the 4 KiB of FP64 they stand for, every access of it one
+// whole 1 KiB run; a private LDS slice turns one chunk per lane into one
+// complex per lane and back. With one or two complex per thread and no LDS
+// the BF16 side moved as 4- or 8-byte words and the FP64 side in strides of
+// 32 bytes: 2^20 sites took 124 (pack) and 126 us (unpack), now 113 and 116;
+// 24^4 sites 42 and 45, now 37 and 38. The caps are from a sweep of 8 to 20
+// wavefronts per CU, or none, at 49,152 to 2,560,000 sites; three or four
+// chunks per lane, 256 threads and the XCD order were slower. A grid that is
+// resident at once (not kThrough) loads cached: its input is small enough to
+// be found in the caches, and nontemporal loads cost the pack of 16,384 sites
+// 15% there.
+#ifndef SU3_WAVES_BF16_CONV
+#define SU3_WAVES_BF16_CONV 14
+#endif
+constexpr int kPackBf16Block = 64, kUnpackBf16Block = 128;
+
 // FP64 complex -> BF16 (re, im), through FP32, each step to nearest even.
-template <int B>
-__global__ __launch_bounds__(B) void pack_bf16(const d2 *__restrict__ src, uint32_t *__restrict__ dst,
-                                                    int64_t n)
+template <bool kThrough>
+__global__ __launch_bounds__(kPackBf16Block) void pack_bf16(const d2 *__restrict__ src, u4 *__restrict__ dst,
+                                                            int64_t chunks)
 {
-    for (int64_t e = (int64_t)blockIdx.x * B + threadIdx.x; e < n; e += (int64_t)gridDim.x * B) {
-        const d2 v = src[e];
-        dst[e] = pack_bf16x2((float)v.x, (float)v.y);
+    __shared__ u4 stage[kPackBf16Block];
+    const int lane = threadIdx.x;
+    const int64_t c0 = (int64_t)blockIdx.x * kPackBf16Block, n = 4 * chunks;
+    d2 v[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int64_t g = 4 * c0 + 64 * i + lane;
+        const d2 *p = src + (g < n ? g : n - 1);   // in bounds; dropped past the end
+        v[i] = kThrough ? ld_stream(p) : *p;
     }
+    uint32_t *words = reinterpret_cast<uint32_t *>(stage);
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+        words[64 * i + lane] = pack_bf16x2((float)v[i].x, (float)v[i].y);
+    wave_sync();
+    store_runs<kThrough, 1>(dst, stage, c0, lane, chunks);
 }
 
 // FP64 links -> rows 0 and 1 in FP32 (V = f2, round to nearest even) or FP64
@@ -358,9 +389,7 @@ __global__ __launch_bounds__(64) void pack_r12(const u4 *__restrict__ src, u4 *_
 #pragma unroll
     for (int i = 0; i < 9; ++i)
         stage[64 * i + lane] = v[i];
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    wave_sync();
     typedef typename std::conditional<sizeof(V) == 8, float, double>::type E;   // element of V
     V o[6];
 #pragma unroll
@@ -368,42 +397,49 @@ __global__ __launch_bounds__(64) void pack_r12(const u4 *__restrict__ src, u4 *_
         const d2 w = __builtin_bit_cast(d2, stage[9 * lane + q]);
         o[q] = V{(E)w.x, (E)w.y};
     }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    wave_sync();
     V *out = reinterpret_cast<V *>(stage) + 6 * lane;
 #pragma unroll
     for (int q = 0; q < 6; ++q)
         out[q] = o[q];
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    wave_sync();
     store_runs<kThrough, kOut>(dst, stage, t * 64 * kOut, lane, nout);
 }
 
 // ------------------------------------------------------------ unpack
+// FP32 complex -> FP64, exact, one complex per thread; nontemporal loads and
+// stores: 6.70 against 6.47 TB/s with plain ones at 2^20 sites.
 template <int B>
 __global__ __launch_bounds__(B) void unpack_f32(const f2 *__restrict__ src, d2 *__restrict__ dst, int64_t n)
 {
     for (int64_t e = (int64_t)blockIdx.x * B + threadIdx.x; e < n; e += (int64_t)gridDim.x * B) {
-        const f2 v = src[e];
-        d2 o = {(double)v.x, (double)v.y};
-        dst[e] = o;
+        const f2 v = ld_stream(src + e);
+        const d2 o = {(double)v.x, (double)v.y};
+        st_stream(dst + e, o);
     }
 }
 
-// BF16 -> FP64, exact; two complex numbers per thread (one 8-byte load, two
-// 16-byte stores). n2 = number of pairs (36 complex per site, so no odd one).
-template <int B>
-__global__ __launch_bounds__(B) void unpack_bf16(const u2 *__restrict__ src, d2 *__restrict__ dst, int64_t n2)
+// BF16 -> FP64, exact.
+template <bool kThrough>
+__global__ __launch_bounds__(kUnpackBf16Block) void unpack_bf16(const u4 *__restrict__ src, d2 *__restrict__ dst,
+                                                                int64_t chunks)
 {
-    for (int64_t e = (int64_t)blockIdx.x * B + threadIdx.x; e < n2; e += (int64_t)gridDim.x * B) {
-        const u2 w = src[e];
-        const d2 o0 = {(double)bf16_lo(w.x), (double)bf16_hi(w.x)};
-        const d2 o1 = {(double)bf16_lo(w.y), (double)bf16_hi(w.y)};
-        dst[2 * e] = o0;
-        dst[2 * e + 1] = o1;
-    }
+    __shared__ u4 stage[kUnpackBf16Block];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int64_t c0 = (int64_t)blockIdx.x * kUnpackBf16Block + 64 * wave, n = 4 * chunks;
+    u4 *my = stage + 64 * wave;
+    const u4 *p = src + (c0 + lane < chunks ? c0 + lane : chunks - 1);   // in bounds; dropped past the end
+    my[lane] = kThrough ? ld_stream(p) : *p;
+    wave_sync();
+    const uint32_t *words = reinterpret_cast<const uint32_t *>(my);
+    uint32_t w[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+        w[i] = words[64 * i + lane];
+    const OutWindow out = out_window(dst + 4 * c0, 16 * (n - 4 * c0));
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+        st_out<kThrough>(out, 16 * (64 * i + lane), d2{(double)bf16_lo(w[i]), (double)bf16_hi(w[i])});
 }
 
 // Rows 0-1 (FP32 or FP64) -> full FP64 link; row 2 = conj(row0 x row1) evaluated in
@@ -435,9 +471,7 @@ __global__ __launch_bounds__(64) void unpack_r12(const u4 *__restrict__ src, u4 
 #pragma unroll
     for (int i = 0; i < kIn; ++i)
         stage[64 * i + lane] = v[i];
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    wave_sync();
     double r[12];
     const V *in = reinterpret_cast<const V *>(stage) + 6 * lane;
 #pragma unroll
@@ -460,15 +494,11 @@ __global__ __launch_bounds__(64) void unpack_r12(const u4 *__restrict__ src, u4 
         const double qi = r0[2 * q] * r1[2 * p + 1] + r0[2 * q + 1] * r1[2 * p];
         o[6 + l] = d2{pr - qr, -(pi - qi)};
     }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    wave_sync();
 #pragma unroll
     for (int q = 0; q < 9; ++q)
         stage[9 * lane + q] = __builtin_bit_cast(u4, o[q]);
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    wave_sync();
     store_runs<kThrough, 9>(dst, stage, t * 64 * 9, lane, nout);
 }
 
@@ -689,6 +719,41 @@ static hipError_t launch_unpack_r12(const void *src, void *dst, int64_t links, h
                     (const u4 *)src, (u4 *)dst, links);
 }
 
+// The BF16 conversions of `chunks` 16-byte chunks of the BF16 side (9 per
+// site), in launches of at most 2^31 threads: one for any lattice of up to 238
+// million sites (a loop inside the pack cost it 7%).
+constexpr int64_t kBf16Chunks = (int64_t)1 << 31;
+
+static hipError_t launch_pack_bf16(const d2 *src, u4 *dst, int64_t chunks, hipStream_t s)
+{
+    static PadCache cache;
+    hipError_t e = hipSuccess;
+    for (int64_t c = 0; c < chunks && e == hipSuccess; c += kBf16Chunks) {
+        const int64_t m = chunks - c < kBf16Chunks ? chunks - c : kBf16Chunks;
+        const int64_t grid = (m + kPackBf16Block - 1) / kPackBf16Block;
+        const LaunchPlan plan = launch_plan(reinterpret_cast<const void *>(pack_bf16<true>), SU3_WAVES_BF16_CONV,
+                                            kPackBf16Block, grid, cache);
+        e = launch_k(plan.one_generation ? pack_bf16<false> : pack_bf16<true>, dim3((unsigned)grid),
+                     dim3(kPackBf16Block), s, plan.pad, src + 4 * c, dst + c, m);
+    }
+    return e;
+}
+
+static hipError_t launch_unpack_bf16(const u4 *src, d2 *dst, int64_t chunks, hipStream_t s)
+{
+    static PadCache cache;
+    hipError_t e = hipSuccess;
+    for (int64_t c = 0; c < chunks && e == hipSuccess; c += kBf16Chunks) {
+        const int64_t m = chunks - c < kBf16Chunks ? chunks - c : kBf16Chunks;
+        const int64_t grid = (m + kUnpackBf16Block - 1) / kUnpackBf16Block;
+        const LaunchPlan plan = launch_plan(reinterpret_cast<const void *>(unpack_bf16<true>), SU3_WAVES_BF16_CONV,
+                                            kUnpackBf16Block, grid, cache);
+        e = launch_k(plan.one_generation ? unpack_bf16<false> : unpack_bf16<true>, dim3((unsigned)grid),
+                     dim3(kUnpackBf16Block), s, plan.pad, src + c, dst + 4 * c, m);
+    }
+    return e;
+}
+
 // precision codes as in su3.h: 0 F64, 1 F32, 2 BF16, 3 R12_F32 (rows 0-1 FP32
 // in, full FP32 out), 4 R12C_F32 (rows 0-1 FP32 in and out), 5 R12_F64 (rows
 // 0-1 FP64 in, full FP64 out). Codes 3 and 4 share the storage of a.
@@ -700,8 +765,7 @@ hipError_t launch_pack(const void *src, void *dst, int64_t sites, int precision,
         return launch_k(pack_f32<64>, dim3(grid_for(elems, 64, kOnePass)), dim3(64), s, 0, (const d2 *)src,
                         (f2 *)dst, elems);
     case 2:
-        return launch_k(pack_bf16<128>, dim3(grid_for(elems, 128, kOnePass)), dim3(128), s, 0, (const d2 *)src,
-                        (uint32_t *)dst, elems);
+        return launch_pack_bf16((const d2 *)src, (u4 *)dst, elems / 4, s);
     case 3:
     case 4:
         return launch_pack_r12<f2>(src, dst, links, s);
@@ -720,8 +784,7 @@ hipError_t launch_unpack(const void *src, void *dst, int64_t sites, int precisio
         return launch_k(unpack_f32<64>, dim3(grid_for(elems, 64, kOnePass)), dim3(64), s, 0, (const f2 *)src, (d2 *)dst,
                         elems);
     case 2:
-        return launch_k(unpack_bf16<256>, dim3(grid_for(elems / 2, 256, kOnePass)), dim3(256), s, 0, (const u2 *)src,
-                        (d2 *)dst, elems / 2);
+        return launch_unpack_bf16((const u4 *)src, (d2 *)dst, elems / 4, s);
     case 3:
     case 4:
         return launch_unpack_r12<f2>(src, dst, links, s);

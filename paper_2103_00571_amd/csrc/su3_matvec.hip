@@ -26,13 +26,6 @@ namespace su3 {
 
 constexpr int kMvBlock = 64;    // one wavefront per workgroup
 
-__device__ __forceinline__ void wave_sync_mv()
-{
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 template <typename S, bool kThrough>
 __global__ __launch_bounds__(kMvBlock) void mat_vec(const u4 *__restrict__ a, const uint64_t *__restrict__ v,
                                                     u4 *__restrict__ w, int64_t sites)
@@ -69,7 +62,7 @@ __global__ __launch_bounds__(kMvBlock) void mat_vec(const u4 *__restrict__ a, co
     vst[lane] = vv[0];
     if (lane < 32)
         vst[64 + lane] = vv[1];
-    wave_sync_mv();
+    wave_sync();
 
     // the lane's unit: R links of site lane / kUnitsPerSite of the tile
     S x[18 * R], vec[6], o[6 * R];
@@ -100,7 +93,7 @@ __global__ __launch_bounds__(kMvBlock) void mat_vec(const u4 *__restrict__ a, co
             o[6 * r + 2 * k] = re;
             o[6 * r + 2 * k + 1] = im;
         }
-    wave_sync_mv();
+    wave_sync();
 #pragma unroll
     for (int i = 0; i < 3; ++i) {
         SV c;
@@ -109,7 +102,7 @@ __global__ __launch_bounds__(kMvBlock) void mat_vec(const u4 *__restrict__ a, co
             c[e] = o[PV * i + e];
         stage[3 * lane + i] = __builtin_bit_cast(u4, c);
     }
-    wave_sync_mv();
+    wave_sync();
     store_runs<kThrough, 3>(w, stage, t * 192, lane, nw);
 }
 

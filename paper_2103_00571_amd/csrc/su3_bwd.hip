@@ -13,10 +13,11 @@
 // to 18 FP64 accumulators. The tiles of a wavefront are spaced a multiple of
 // 3 tiles (192 rows, a multiple of the 12 rows of a site) apart, so a lane
 // keeps one row position, hence one link and one accumulator set, on every
-// tile. A workgroup of 3 wavefronts takes kSteps steps each; in FP64 the
-// workgroups are taken in batches of 256 and step k of every workgroup of a
-// batch lies in one contiguous block (phase striping), which keeps the
-// workgroups that run together on one contiguous front.
+// tile. A workgroup of 3 wavefronts takes kSteps steps each, 1, 2 or 4 by the
+// lattice size; in most forms the workgroups are taken in batches of 256 and
+// step k of every workgroup of a batch lies in one contiguous block (phase
+// striping), which keeps the workgroups that run together on one contiguous
+// front.
 // At the end the lanes' accumulators are summed in a fixed order: per row
 // position within the wavefront (lanes in increasing order), then per link
 // over the workgroup's wavefronts and the link's three rows. Each workgroup
@@ -25,71 +26,62 @@
 // components 4u .. 4u+3 at 4 (u * groups + g), so each workgroup writes 18
 // whole 32-byte sectors rather than 72 scattered doubles (a scattered
 // 8-byte store costs a whole sector of HBM writes).
-// Stage 2 reduces the partials of each of the 72 real components in two
-// fixed-order levels: bwd_chunk_sums adds runs of kChunk consecutive partials
-// of a quad's 4 components (8 per thread, then a shuffle tree per wavefront
-// and the wavefronts in order), bwd_reduce adds the run sums, stored
-// component-major (one wavefront per component: a strided loop, then a
-// shuffle tree). With a single run per component the first level writes dB
-// itself and the second is not launched. Both levels keep every load of a
+// Stage 2 (bwd_sum) reduces the partials of each of the 72 real components in
+// two fixed-order levels in one launch: runs of kChunk consecutive partials
+// of a quad's 4 components, one workgroup each, then the run sums, by the
+// last workgroup of the quad to arrive. Both levels keep every load of a
 // thread in flight at once, so stage 2 costs a few microseconds at any
 // lattice size.
 // The number of workgroups of every stage depends only on the number of sites
 // and the form, so the rounding sequence, and every bit of dB, is the same on
-// every run and every device. No atomics.
+// every run and every device. The only atomics are stage 2's arrival counts,
+// which decide who adds the run sums, not in which order.
 #include "su3_internal.hpp"
 
 namespace su3 {
 
 constexpr int kBwdWaves = 3;                 // wavefronts per workgroup
 constexpr int kBwdThreads = 64 * kBwdWaves;
-// Steps per wavefront and resident wavefronts per CU for stage 1 (0: as many
-// as fit), from sweeps at L=32 over 1 to 128 steps, caps of 6, 9 and 12
-// wavefronts and batches of 32 to 3072 workgroups (or none). More steps
-// amortise the closing reduction and cut the partials stage 2 reads; fewer
-// shorten the drain at the end of the grid and keep the workgroups from
-// drifting apart in memory.
-#ifndef SU3_BWD_TILES_F64
-#define SU3_BWD_TILES_F64 4
-#endif
-#ifndef SU3_BWD_TILES_F32
-#define SU3_BWD_TILES_F32 2
-#endif
-#ifndef SU3_BWD_WAVES_F64
-#define SU3_BWD_WAVES_F64 9
-#endif
-#ifndef SU3_BWD_WAVES_F32
-#define SU3_BWD_WAVES_F32 12
-#endif
-// Tile order of stage 1: 0, workgroup g takes tile group g; 1, the
-// XCD-contiguous order of the forward kernels (xcd_order).
-#ifndef SU3_BWD_XCD_ORDER
-#define SU3_BWD_XCD_ORDER 0
-#endif
-// Phase striping of stage 1 (0: off): the workgroups are taken in batches
-// of kBatch, and step k of every workgroup of a batch lies in one
-// contiguous block of the batch's tiles, so the workgroups that run at the
-// same time stream one contiguous front instead of each its own run.
-#ifndef SU3_BWD_BATCH_F64
-#define SU3_BWD_BATCH_F64 256
-#endif
-#ifndef SU3_BWD_BATCH_F32
-#define SU3_BWD_BATCH_F32 0
-#endif
-
-// The two forms: kSub 64-row tiles per step (3 chunks per lane of each
-// array), kSteps steps per wavefront, phase-striping batch kBatch.
-struct BwdF64 {
-    typedef double S;
-    static constexpr int kSub = 1, kSteps = SU3_BWD_TILES_F64, kBatch = SU3_BWD_BATCH_F64;
+// Forms of stage 1: kSub 64-row tiles per step (3 chunks per lane of each
+// array), kSteps steps per wavefront, at most kWaves resident wavefronts per CU.
+// More steps amortise the closing reduction and cut the partials stage 2
+// reads; fewer shorten the drain at the end of the grid and spread a small
+// lattice over more CUs.
+// kBatch, phase striping (0: off): the workgroups are taken in batches of
+// kBatch, and step k of every workgroup of a batch lies in one contiguous
+// block of the batch's tiles, so the workgroups that run at the same time
+// stream one contiguous front instead of each its own run.
+// kEarly: a wavefront's first loads are issued before the barrier that
+// publishes b, so they do not wait for it.
+template <typename S_, int kSub_, int kSteps_, int kBatch_, bool kEarly_, int kWaves_>
+struct BwdForm {
+    typedef S_ S;
+    static constexpr int kSub = kSub_, kSteps = kSteps_, kBatch = kBatch_, kWaves = kWaves_;
+    static constexpr bool kEarly = kEarly_;
+    static constexpr int kTiles = kBwdWaves * kSub * kSteps;   // 64-row tiles per workgroup
 };
-struct BwdF32 {
-    typedef float S;
-    static constexpr int kSub = 2, kSteps = SU3_BWD_TILES_F32, kBatch = SU3_BWD_BATCH_F32;
-};
+// Which form takes which lattice, by the last site count of each (sweeps of 1,
+// 2 and 4 steps, caps of 9 and 12, batches of 0 and 256 and both kEarly at 16
+// sizes; microseconds, both stages, against 4 steps, a cap of 9 and a batch of
+// 256 in FP64 and 2 steps and a cap of 12 in FP32, both without kEarly).
+// The lines at 16,384 to 131,072 sites lie where the whole grid is resident
+// at once with 1, 2 or 4 steps.
+//  FP64: 4,096 sites 6.2 / 8.4, 16,384 9.6 / 10.2, 20,000 10.8 / 12.0, 131,072
+//  42.6 / 43.2, 160,000 50.4 / 52.1, 331,776 97 / 98, 2^20 288 / 291, 2,000,000
+//  546 / 556 (2 steps there: 567).
+//  FP32: 4,096 sites 6.6 / 7.5, 32,768 9.9 / 10.7, 100,000 20.7 / 21.2, 331,776
+//  52.3 / 52.9; above 700,000 sites kEarly loses 1-5% and a batch 1-2%.
+typedef BwdForm<double, 1, 1, 0, true, 12> BwdF64x1;     // to 16,384 sites
+typedef BwdForm<double, 1, 2, 256, true, 12> BwdF64x2;   // to 32,768 and from 131,072 to 400,000
+typedef BwdForm<double, 1, 4, 256, true, 9> BwdF64x4;    // to 131,072 and from 400,000
+typedef BwdForm<float, 2, 1, 0, true, 12> BwdF32x1;      // to 32,768
+typedef BwdForm<float, 2, 2, 256, true, 12> BwdF32x2;    // to 700,000
+typedef BwdForm<float, 2, 2, 0, false, 12> BwdF32Large;  // above
+constexpr int64_t kLast64[] = {16384, 32768, 131072, 400000};
+constexpr int64_t kLast32[] = {32768, 700000};
 constexpr int kRowsPerSite = 12;
 
-// Stage 2, first level: threads per workgroup and partials per thread.
+// Stage 2: threads per workgroup and partials per thread of one run.
 #ifndef SU3_BWD_CHUNK_THREADS
 #define SU3_BWD_CHUNK_THREADS 256
 #endif
@@ -141,7 +133,8 @@ __device__ __forceinline__ void row_to_stage(u4 *st, int q, int lane, const floa
 template <class F>
 __global__ __launch_bounds__(kBwdThreads) void bwd_tiles(const u4 *__restrict__ a, const typename F::S *__restrict__ b,
                                                          const u4 *__restrict__ dc, u4 *__restrict__ da,
-                                                         double *__restrict__ ws, int64_t rows, int64_t groups)
+                                                         double *__restrict__ ws, uint32_t *__restrict__ counts,
+                                                         int64_t rows, int64_t groups)
 {
     typedef typename F::S S;
     constexpr int kSub = F::kSub;                     // 64-row tiles per step
@@ -159,10 +152,10 @@ __global__ __launch_bounds__(kBwdThreads) void bwd_tiles(const u4 *__restrict__ 
     u4 *stg = reinterpret_cast<u4 *>(tilebuf[wv]);    // dC at [0, 192), A at [192, 384)
     double *red = reinterpret_cast<double *>(tilebuf[wv]);
     // this workgroup's tile group; its partial goes to slot grp
-    const int64_t grp = SU3_BWD_XCD_ORDER ? xcd_order(blockIdx.x, gridDim.x) : (int64_t)blockIdx.x;
+    const int64_t grp = blockIdx.x;
     // the wavefront's first 64-row tile t0; it takes t0 + D i for
     // i < kSub * kSteps (D a multiple of 3)
-    constexpr int kPer = kBwdWaves * kSub * kSteps;   // tiles per workgroup
+    constexpr int kPer = F::kTiles;
     int64_t t0, D;
     if constexpr (F::kBatch > 0) {
         constexpr int kB = F::kBatch;
@@ -175,23 +168,6 @@ __global__ __launch_bounds__(kBwdThreads) void bwd_tiles(const u4 *__restrict__ 
         D = kBwdWaves;
     }
     const int64_t nchunks = rows * 6 * (int64_t)sizeof(S) / 16;
-
-    if (threadIdx.x < 72)
-        bsh[threadIdx.x] = b[threadIdx.x];
-    __syncthreads();
-
-    const int pos = (int)((t0 * 64 + lane) % kRowsPerSite);   // row position in the site
-    const int j = pos / 3;                                     // its link
-    S br[9], bi[9];
-#pragma unroll
-    for (int q = 0; q < 9; ++q) {
-        br[q] = bsh[2 * (9 * j + q)];
-        bi[q] = bsh[2 * (9 * j + q) + 1];
-    }
-    double acc[18];
-#pragma unroll
-    for (int v = 0; v < 18; ++v)
-        acc[v] = 0.0;
 
     // Global chunk of step-chunk c (c = 64 i + lane, i < 3) of the step that
     // starts at tile ts: sub-tile c / CT, chunk c mod CT of it.
@@ -213,7 +189,30 @@ __global__ __launch_bounds__(kBwdThreads) void bwd_tiles(const u4 *__restrict__ 
             va[i] = ld_stream(a + gc);
         }
     };
-    if (t0 * 64 < rows)
+    // b before the first step: vector memory operations retire in order, so the
+    // barrier that publishes b in LDS waits for the b load only while the step
+    // is in flight.
+    const S bv = threadIdx.x < 72 ? b[threadIdx.x] : S(0);
+    if (F::kEarly)
+        load_step(t0);
+    if (threadIdx.x < 72)
+        bsh[threadIdx.x] = bv;
+    if (blockIdx.x == 0 && threadIdx.x < 18)
+        counts[threadIdx.x] = 0;   // for stage 2
+    __syncthreads();
+    const int pos = (int)((t0 * 64 + lane) % kRowsPerSite);   // row position in the site
+    const int j = pos / 3;                                     // its link
+    S br[9], bi[9];
+#pragma unroll
+    for (int q = 0; q < 9; ++q) {
+        br[q] = bsh[2 * (9 * j + q)];
+        bi[q] = bsh[2 * (9 * j + q) + 1];
+    }
+    double acc[18];
+#pragma unroll
+    for (int v = 0; v < 18; ++v)
+        acc[v] = 0.0;
+    if (!F::kEarly)
         load_step(t0);
     for (int k = 0; k < kSteps; ++k) {
         const int64_t ts = t0 + D * kSub * k;   // the step's first tile
@@ -324,20 +323,34 @@ __global__ __launch_bounds__(kBwdThreads) void bwd_tiles(const u4 *__restrict__ 
     }
 }
 
-// grid = (chunks, 18): workgroup (c, u) adds partials c*kChunk .. c*kChunk +
-// kChunk - 1 of the 4 components of quad u and writes run sums
-// ws2[q * chunks + c] for q = 4u .. 4u+3. Thread t adds partials t,
-// t + kChunkThreads, ... in order; then, per component, a binary tree across
+// Stage 2, grid = (chunks, 18): workgroup (c, u) adds partials c*kChunk ..
+// c*kChunk + kChunk - 1 of the 4 components of quad u. Thread t adds partials
+// t, t + kChunkThreads, ... in order; then, per component, a binary tree across
 // the lanes of each wavefront pairs lane t with t + w for w = 32, 16, ..., 1,
-// and the wavefront sums are added in wavefront order.
-__global__ __launch_bounds__(kChunkThreads) void bwd_chunk_sums(const double *__restrict__ ws,
-                                                                double *__restrict__ ws2, int64_t groups,
-                                                                int64_t chunks)
+// and the wavefront sums are added in wavefront order. With one run that is
+// dB. Otherwise the workgroup leaves its run's 4 sums in the run's first
+// partial slot, whose contents it has read, and counts itself in; the last
+// one of quad u adds the run sums in the same fixed order, whichever
+// workgroup it is: lane t of wavefront e takes runs t, t + 64, ... of component
+// e in order, then the tree.
+// Run sums and counts move at agent scope (write-through stores, loads and
+// atomics at the memory side), each store complete before the count, so no
+// cache has to be written back or invalidated; a release fence would write
+// back the XCD's whole L2 in every workgroup, which made one launch slower
+// than two. Two launches took 9.3 us (4.7 and 4.6) after stage 1 in FP64, at
+// L = 32 and at 24^4 alike; this one takes 5.8 and 5.4.
+__global__ __launch_bounds__(kChunkThreads) void bwd_sum(double *__restrict__ ws, double *__restrict__ db,
+                                                         uint32_t *__restrict__ counts, int64_t groups,
+                                                         int64_t chunks)
 {
     constexpr int kW = kChunkThreads / 64;
+    static_assert(kW >= 4, "one wavefront per component in the last workgroup");
     __shared__ double red[4][kW];
+    __shared__ uint32_t arrived;
     const int64_t c = blockIdx.x;
-    const d2 *src = reinterpret_cast<const d2 *>(ws + 4 * (int64_t)blockIdx.y * groups);
+    const int u = blockIdx.y, wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    double *quad = ws + 4 * (int64_t)u * groups;   // 4 doubles per workgroup of stage 1
+    const d2 *src = reinterpret_cast<const d2 *>(quad);
     d2 v[kChunkLoads][2];
 #pragma unroll
     for (int i = 0; i < kChunkLoads; ++i) {
@@ -359,107 +372,126 @@ __global__ __launch_bounds__(kChunkThreads) void bwd_chunk_sums(const double *__
 #pragma unroll
         for (int e = 0; e < 4; ++e)
             sum[e] += __shfl_down(sum[e], w, 64);
-    const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    if (kW == 1) {
-        // after the tree lane 0 holds the four sums
-        if (lane == 0) {
-#pragma unroll
-            for (int e = 0; e < 4; ++e)
-                ws2[(int64_t)(4 * blockIdx.y + e) * chunks + c] = sum[e];
-        }
-        return;
-    }
     if (lane == 0) {
 #pragma unroll
         for (int e = 0; e < 4; ++e)
             red[e][wv] = sum[e];
     }
     __syncthreads();
+    double total = 0.0;
     if (threadIdx.x < 4) {
-        double t = red[threadIdx.x][0];
+        total = red[threadIdx.x][0];
 #pragma unroll
         for (int w2 = 1; w2 < kW; ++w2)
-            t += red[threadIdx.x][w2];
-        ws2[(int64_t)(4 * blockIdx.y + threadIdx.x) * chunks + c] = t;
+            total += red[threadIdx.x][w2];
     }
-}
-
-// grid = 72 workgroups of one wavefront, one per real component of dB; the
-// input holds `groups` values per component, component-major (the run sums
-// of stage 2a). Lane t adds values t, t + 64, ... in order, then a binary
-// tree across the lanes pairs lane t with t + w for w = 32, 16, ..., 1.
-__global__ __launch_bounds__(64) void bwd_reduce(const double *__restrict__ ws, double *__restrict__ db,
-                                                 int64_t groups)
-{
-    const int q = blockIdx.x;
-    double sum = 0.0;
-    for (int64_t g = threadIdx.x; g < groups; g += 64)
-        sum += ws[(int64_t)q * groups + g];
+    if (chunks == 1) {
+        if (threadIdx.x < 4)
+            db[4 * u + threadIdx.x] = total;
+        return;
+    }
+    if (wv == 0) {
+        if (lane < 4)
+            __hip_atomic_store(quad + 4 * c * kChunk + lane, total, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the sums have reached memory
+        if (lane == 0)
+            arrived = __hip_atomic_fetch_add(counts + u, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    __syncthreads();
+    if (arrived != (uint32_t)chunks - 1 || wv >= 4)
+        return;
+    double x = 0.0;
+    for (int64_t k = lane; k < chunks; k += 64)
+        x += __hip_atomic_load(quad + 4 * k * kChunk + wv, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 #pragma unroll
     for (int w = 32; w > 0; w >>= 1)
-        sum += __shfl_down(sum, w, 64);
-    if (threadIdx.x == 0)
-        db[q] = sum;
+        x += __shfl_down(x, w, 64);
+    if (lane == 0)
+        db[4 * u + wv] = x;
 }
-constexpr int kReduceThreads = 64;
+
+// dB of an empty lattice.
+__global__ __launch_bounds__(128) void bwd_zero(double *__restrict__ db)
+{
+    if (threadIdx.x < 72)
+        db[threadIdx.x] = 0.0;
+}
+
+// The 64-row tiles of one workgroup of stage 1 for a lattice of n sites.
+static int64_t tiles_per_group(int64_t n, int precision)
+{
+    if (precision == 0)
+        return n <= kLast64[0]                       ? BwdF64x1::kTiles
+               : n <= kLast64[1]                     ? BwdF64x2::kTiles
+               : n <= kLast64[2] || n > kLast64[3] ? BwdF64x4::kTiles
+                                                     : BwdF64x2::kTiles;
+    return n <= kLast32[0] ? BwdF32x1::kTiles : BwdF32x2::kTiles;   // and BwdF32Large
+}
 
 // Workgroups of stage 1 for `sites` (a function of the size and form only).
 int64_t bwd_groups(int64_t sites, int precision)
 {
-    const int64_t tiles = (sites * kRowsPerSite + 63) / 64;
-    const int64_t per = (int64_t)kBwdWaves * (precision == 0 ? BwdF64::kSub * BwdF64::kSteps
-                                                              : BwdF32::kSub * BwdF32::kSteps);
+    const int64_t tiles = (sites * kRowsPerSite + 63) / 64, per = tiles_per_group(sites, precision);
     return (tiles + per - 1) / per;
 }
 
 static int64_t bwd_chunks(int64_t groups) { return (groups + kChunk - 1) / kChunk; }
 
+// The partials, and as many doubles as there are run sums: stage 2 keeps its
+// 18 counts (4 bytes each) there. A form with fewer steps makes more groups,
+// so the groups do not grow with the sites everywhere; the workspace does, and
+// one that is large enough for a lattice is large enough for any smaller one.
 int64_t bwd_workspace_doubles(int64_t sites, int precision)
 {
-    const int64_t groups = bwd_groups(sites, precision);
+    int64_t groups = bwd_groups(sites, precision);
+    auto at_least = [&](const int64_t *last, int count) {
+        for (int i = 0; i < count; ++i)
+            if (last[i] < sites && bwd_groups(last[i], precision) > groups)
+                groups = bwd_groups(last[i], precision);
+    };
+    if (precision == 0)
+        at_least(kLast64, sizeof(kLast64) / sizeof(kLast64[0]));
+    else
+        at_least(kLast32, sizeof(kLast32) / sizeof(kLast32[0]));
     return 72 * (groups + bwd_chunks(groups));
 }
 
 int bwd_block_threads() { return kBwdThreads; }
 
+template <class F>
+static hipError_t launch_tiles_f(const void *a, const void *b, const void *dc, void *da, int64_t sites, double *ws,
+                                 uint32_t *counts, int64_t groups, hipStream_t s)
+{
+    static PadCache cache;
+    const LaunchPlan plan =
+        launch_plan(reinterpret_cast<const void *>(bwd_tiles<F>), F::kWaves, kBwdThreads, groups, cache);
+    return launch_k(bwd_tiles<F>, dim3((unsigned)groups), dim3(kBwdThreads), s, plan.pad, (const u4 *)a,
+                    (const typename F::S *)b, (const u4 *)dc, (u4 *)da, ws, counts, sites * kRowsPerSite, groups);
+}
+
 hipError_t launch_bwd(const void *a, const void *b, const void *dc, void *da, double *db, int64_t sites,
                       int precision, double *ws, hipStream_t s)
 {
-    static PadCache cache64, cache32;
     const int64_t groups = bwd_groups(sites, precision), chunks = bwd_chunks(groups);
-    double *ws2 = ws + 72 * groups;
+    const int64_t per = tiles_per_group(sites, precision);
+    uint32_t *counts = reinterpret_cast<uint32_t *>(ws + 72 * groups);
     hipError_t e;
-    if (precision == 0) {
-        const LaunchPlan plan = launch_plan(reinterpret_cast<const void *>(bwd_tiles<BwdF64>), SU3_BWD_WAVES_F64,
-                                            kBwdThreads, groups, cache64);
-        e = launch_k(bwd_tiles<BwdF64>, dim3((unsigned)groups), dim3(kBwdThreads), s, plan.pad, (const u4 *)a,
-                     (const double *)b, (const u4 *)dc, (u4 *)da, ws, sites * kRowsPerSite, groups);
-    } else {
-        const LaunchPlan plan = launch_plan(reinterpret_cast<const void *>(bwd_tiles<BwdF32>), SU3_BWD_WAVES_F32,
-                                            kBwdThreads, groups, cache32);
-        e = launch_k(bwd_tiles<BwdF32>, dim3((unsigned)groups), dim3(kBwdThreads), s, plan.pad, (const u4 *)a,
-                     (const float *)b, (const u4 *)dc, (u4 *)da, ws, sites * kRowsPerSite, groups);
-    }
+    if (precision == 0)
+        e = (per == BwdF64x1::kTiles   ? launch_tiles_f<BwdF64x1>
+             : per == BwdF64x2::kTiles ? launch_tiles_f<BwdF64x2>
+                                       : launch_tiles_f<BwdF64x4>)(a, b, dc, da, sites, ws, counts, groups, s);
+    else
+        e = (per == BwdF32x1::kTiles    ? launch_tiles_f<BwdF32x1>
+             : sites <= kLast32[1] ? launch_tiles_f<BwdF32x2>
+                                        : launch_tiles_f<BwdF32Large>)(a, b, dc, da, sites, ws, counts, groups, s);
     if (e != hipSuccess)
         return e;
-    // With a single run per component (groups <= kChunk) the run sums are dB
-    // itself, component-major: the first level writes them to db directly.
-    if (chunks == 1)
-        return launch_k(bwd_chunk_sums, dim3(1, 18), dim3(kChunkThreads), s, 0, (const double *)ws, db, groups,
-                        (int64_t)1);
-    e = launch_k(bwd_chunk_sums, dim3((unsigned)chunks, 18), dim3(kChunkThreads), s, 0, (const double *)ws, ws2,
-                 groups, chunks);
-    if (e != hipSuccess)
-        return e;
-    return launch_k(bwd_reduce, dim3(72), dim3(kReduceThreads), s, 0, (const double *)ws2, db, chunks);
+    return launch_k(bwd_sum, dim3((unsigned)chunks, 18), dim3(kChunkThreads), s, 0, ws, db, counts, groups, chunks);
 }
 
-// An empty lattice has dB = 0: the second stage over zero partials writes
-// zeros (a kernel rather than a memset, so the call is safe to capture).
-hipError_t launch_bwd_zero(double *db, hipStream_t s)
-{
-    return launch_k(bwd_reduce, dim3(72), dim3(kReduceThreads), s, 0, (const double *)nullptr, db, (int64_t)0);
-}
+// An empty lattice has dB = 0 (a kernel rather than a memset, so the call is
+// safe to capture).
+hipError_t launch_bwd_zero(double *db, hipStream_t s) { return launch_k(bwd_zero, dim3(1), dim3(128), s, 0, db); }
 
 // ---- the library-owned workspace of su3_mult_nn_bwd_noalloc ---------------
 // A fixed device array (each device the library runs on holds its own copy

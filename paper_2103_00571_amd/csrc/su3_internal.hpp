@@ -237,8 +237,8 @@ bool stream_shape_supported(int in_a, int in_b, int out);
 hipError_t launch_stream_shape(const void *a, const void *b, void *c, int64_t tiles, int in_a, int in_b, int out,
                                int waves_per_cu, int tile_order, hipStream_t s);
 // Adjoint: stage 1 writes per-workgroup partial sums of db into ws (72 x
-// bwd_groups doubles, in 32-byte quads of components), stage 2 reduces them in a fixed order
-// through run sums stored after them; bwd_workspace_doubles is the total.
+// bwd_groups doubles, in 32-byte quads of components), stage 2 reduces them
+// in a fixed order; bwd_workspace_doubles is the workspace of both.
 int64_t bwd_groups(int64_t sites, int precision);
 int64_t bwd_workspace_doubles(int64_t sites, int precision);
 int bwd_block_threads();

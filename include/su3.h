@@ -68,7 +68,7 @@
 extern "C" {
 #endif
 
-#define SU3_ABI_VERSION 6
+#define SU3_ABI_VERSION 7
 
 /* storage form codes */
 enum su3_precision {
@@ -254,6 +254,21 @@ size_t su3_mult_nn_bwd_workspace_bytes(int64_t sites, int precision);
 int su3_mult_nn_bwd(const void *a, const void *b, const void *dc, void *da,
                     double *db_f64, int64_t sites, int precision, void *ws,
                     size_t ws_bytes, void *stream);
+
+/*
+ * The gradients in the types of their inputs, for differentiable programs.
+ * db is stored in the type of b: 4x3x3 complex double for SU3_F64, and for
+ * SU3_F32 4x3x3 complex float, the FP64 sum rounded once to nearest even. da
+ * may be NULL, for callers that hold a fixed (the lattice is data, the four
+ * matrices are fitted to it): then a and dc are read, nothing per site is
+ * written, and b is not used and may be NULL; db is then summed in another
+ * fixed order, equally a function of `sites` only. (da alone is su3_mult_na of
+ * dc and b.) db needs 8-byte (SU3_F64) or 4-byte (SU3_F32) alignment.
+ * Otherwise arguments, workspace, zero sites and errors are as su3_mult_nn_bwd.
+ */
+int su3_mult_nn_grad(const void *a, const void *b, const void *dc, void *da, void *db,
+                     int64_t sites, int precision, void *ws, size_t ws_bytes,
+                     void *stream);
 
 /*
  * Allocation-free variant of su3_mult_nn_bwd, for callers that cannot

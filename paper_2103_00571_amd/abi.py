@@ -17,7 +17,7 @@ _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.environ.get("SU3_LIB_PATH") or os.path.join(_HERE, "libsu3.so")
 
 # su3.h constants
-ABI_VERSION = 6
+ABI_VERSION = 7
 SU3_F64, SU3_F32, SU3_BF16, SU3_R12_F32, SU3_R12C_F32, SU3_R12_F64 = 0, 1, 2, 3, 4, 5
 SU3_OK = 0
 SU3_ERR_NULL, SU3_ERR_SIZE, SU3_ERR_ALIGN, SU3_ERR_PRECISION = -1, -2, -3, -4
@@ -44,6 +44,7 @@ SIGNATURES = {
     "su3_unpack": ([_P, _P, _I64, _I, _P], _I),
     "su3_mult_nn_bwd_workspace_bytes": ([_I64, _I], _SZ),
     "su3_mult_nn_bwd": ([_P, _P, _P, _P, _P, _I64, _I, _P, _SZ, _P], _I),
+    "su3_mult_nn_grad": ([_P, _P, _P, _P, _P, _I64, _I, _P, _SZ, _P], _I),
     "su3_mult_nn_bwd_noalloc": ([_P, _P, _P, _P, _P, _I64, _I, _P], _I),
     "su3_stream_copy": ([_P, _P, _I64, _P], _I),
     "su3_stream_shape": ([_P, _P, _P, _I64, _I, _I, _I, _I, _I, _P], _I),
@@ -157,6 +158,11 @@ def su3_mult_nn_bwd_workspace_bytes(sites: int, precision: int) -> int:
 def su3_mult_nn_bwd(a: int, b: int, dc: int, da: int, db_f64: int, sites: int, precision: int,
                     ws: int, ws_bytes: int, stream: int) -> int:
     return lib.su3_mult_nn_bwd(a, b, dc, da, db_f64, sites, precision, ws, ws_bytes, stream)
+
+
+def su3_mult_nn_grad(a: int, b: int, dc: int, da: int, db: int, sites: int, precision: int, ws: int, ws_bytes: int,
+                     stream: int) -> int:
+    return lib.su3_mult_nn_grad(a, b, dc, da, db, sites, precision, ws, ws_bytes, stream)
 
 
 def su3_mult_nn_bwd_noalloc(a: int, b: int, dc: int, da: int, db_f64: int, sites: int, precision: int,

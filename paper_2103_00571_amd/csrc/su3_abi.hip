@@ -304,11 +304,12 @@ size_t su3_mult_nn_bwd_workspace_bytes(int64_t sites, int precision)
     return (size_t)bwd_workspace_doubles(sites, precision) * sizeof(double);
 }
 
-// Validation shared by both adjoint entry points. ws is the caller's
-// workspace (checked for size, alignment and overlap) unless own_ws is set,
-// in which case the library's own array is used and only its size is checked.
-static int check_bwd(const void *a, const void *b, const void *dc, const void *da, const double *db_f64, int64_t sites,
-                     int precision, const void *ws, size_t ws_bytes, bool own_ws)
+// Validation shared by the adjoint entry points. ws is the caller's workspace
+// (checked for size, alignment and overlap) unless own_ws is set, in which
+// case the library's own array is used and only its size is checked. db holds
+// db_bytes bytes; with want_da false, b and da are not used.
+static int check_bwd(const void *a, const void *b, const void *dc, const void *da, const void *db, int64_t db_bytes,
+                     bool want_da, int64_t sites, int precision, const void *ws, size_t ws_bytes, bool own_ws)
 {
     if (precision != SU3_F64 && precision != SU3_F32)
         return SU3_ERR_PRECISION;
@@ -316,9 +317,9 @@ static int check_bwd(const void *a, const void *b, const void *dc, const void *d
     form_of(precision, f);
     if (sites < 0 || sites > kMaxSites || !grid_fits(bwd_groups(sites, precision), bwd_block_threads()))
         return SU3_ERR_SIZE;
-    if (!db_f64)
+    if (!db)
         return SU3_ERR_NULL;
-    if (sites > 0 && (!a || !b || !dc || !da))
+    if (sites > 0 && (!a || !dc || (want_da && (!b || !da))))
         return SU3_ERR_NULL;
     const size_t need = su3_mult_nn_bwd_workspace_bytes(sites, precision);
     if (own_ws) {
@@ -327,19 +328,23 @@ static int check_bwd(const void *a, const void *b, const void *dc, const void *d
     } else if (sites > 0 && (!ws || ws_bytes < need)) {
         return SU3_ERR_WORKSPACE;
     }
-    if (!aligned(db_f64, 8))
+    if (!aligned(db, db_bytes / 72))
         return SU3_ERR_ALIGN;
-    if (sites > 0 && (!aligned(a, 16) || !aligned(dc, 16) || !aligned(da, 16) || !aligned(b, f.b_align) ||
-                      (!own_ws && !aligned(ws, 16))))
+    if (sites == 0)
+        return SU3_OK;
+    if (!aligned(a, 16) || !aligned(dc, 16) || (want_da && (!aligned(da, 16) || !aligned(b, f.b_align))) ||
+        (!own_ws && !aligned(ws, 16)))
         return SU3_ERR_ALIGN;
     const int64_t n = sites * f.a_site;
-    if (sites > 0 && (overlap(da, n, a, n) || overlap(da, n, dc, n) || overlap(da, n, b, f.b_total) ||
-                      overlap(db_f64, 576, a, n) || overlap(db_f64, 576, dc, n) || overlap(db_f64, 576, da, n) ||
-                      overlap(db_f64, 576, b, f.b_total)))
+    if (overlap(db, db_bytes, a, n) || overlap(db, db_bytes, dc, n))
         return SU3_ERR_OVERLAP;
-    if (sites > 0 && !own_ws &&
-        (overlap(ws, (int64_t)need, a, n) || overlap(ws, (int64_t)need, dc, n) || overlap(ws, (int64_t)need, da, n) ||
-         overlap(ws, (int64_t)need, b, f.b_total) || overlap(ws, (int64_t)need, db_f64, 576)))
+    if (want_da && (overlap(da, n, a, n) || overlap(da, n, dc, n) || overlap(da, n, b, f.b_total) ||
+                    overlap(db, db_bytes, da, n) || overlap(db, db_bytes, b, f.b_total)))
+        return SU3_ERR_OVERLAP;
+    if (!own_ws && (overlap(ws, (int64_t)need, a, n) || overlap(ws, (int64_t)need, dc, n) ||
+                    overlap(ws, (int64_t)need, db, db_bytes)))
+        return SU3_ERR_OVERLAP;
+    if (!own_ws && want_da && (overlap(ws, (int64_t)need, da, n) || overlap(ws, (int64_t)need, b, f.b_total)))
         return SU3_ERR_OVERLAP;
     return SU3_OK;
 }
@@ -347,29 +352,44 @@ static int check_bwd(const void *a, const void *b, const void *dc, const void *d
 int su3_mult_nn_bwd(const void *a, const void *b, const void *dc, void *da, double *db_f64, int64_t sites,
                     int precision, void *ws, size_t ws_bytes, void *stream)
 {
-    const int st = check_bwd(a, b, dc, da, db_f64, sites, precision, ws, ws_bytes, false);
+    const int st = check_bwd(a, b, dc, da, db_f64, 576, true, sites, precision, ws, ws_bytes, false);
     if (st != SU3_OK)
         return st;
     hipStream_t s = (hipStream_t)stream;
     if (sites == 0)
-        return status_of(launch_bwd_zero(db_f64, s));
-    return status_of(launch_bwd(a, b, dc, da, db_f64, sites, precision, (double *)ws, s));
+        return status_of(launch_bwd_zero(db_f64, false, s));
+    return status_of(launch_bwd(a, b, dc, da, db_f64, false, sites, precision, (double *)ws, s));
+}
+
+int su3_mult_nn_grad(const void *a, const void *b, const void *dc, void *da, void *db, int64_t sites, int precision,
+                     void *ws, size_t ws_bytes, void *stream)
+{
+    const bool f32 = precision == SU3_F32;
+    const int st =
+        check_bwd(a, b, dc, da, db, f32 ? 288 : 576, da != nullptr, sites, precision, ws, ws_bytes, false);
+    if (st != SU3_OK)
+        return st;
+    hipStream_t s = (hipStream_t)stream;
+    if (sites == 0)
+        return status_of(launch_bwd_zero(db, f32, s));
+    return status_of(da ? launch_bwd(a, b, dc, da, db, f32, sites, precision, (double *)ws, s)
+                        : launch_db(a, dc, db, f32, sites, precision, (double *)ws, s));
 }
 
 int su3_mult_nn_bwd_noalloc(const void *a, const void *b, const void *dc, void *da, double *db_f64, int64_t sites,
                             int precision, void *stream)
 {
-    const int st = check_bwd(a, b, dc, da, db_f64, sites, precision, nullptr, 0, true);
+    const int st = check_bwd(a, b, dc, da, db_f64, 576, true, sites, precision, nullptr, 0, true);
     if (st != SU3_OK)
         return st;
     hipStream_t s = (hipStream_t)stream;
     if (sites == 0)
-        return status_of(launch_bwd_zero(db_f64, s));
+        return status_of(launch_bwd_zero(db_f64, false, s));
     double *ws = nullptr;
     const hipError_t e = bwd_scratch(&ws);
     if (e != hipSuccess)
         return SU3_ERR_HIP;
-    return status_of(launch_bwd(a, b, dc, da, db_f64, sites, precision, ws, s));
+    return status_of(launch_bwd(a, b, dc, da, db_f64, false, sites, precision, ws, s));
 }
 
 int su3_stream_copy(const void *src, void *dst, int64_t bytes, void *stream)

@@ -77,6 +77,9 @@ typedef BwdForm<double, 1, 4, 256, true, 9> BwdF64x4;    // to 131,072 and from 
 typedef BwdForm<float, 2, 1, 0, true, 12> BwdF32x1;      // to 32,768
 typedef BwdForm<float, 2, 2, 256, true, 12> BwdF32x2;    // to 700,000
 typedef BwdForm<float, 2, 2, 0, false, 12> BwdF32Large;  // above
+// dB alone (kSteps 0: the step count is a launch argument, db_steps).
+typedef BwdForm<double, 1, 0, 256, true, 9> DbF64;
+typedef BwdForm<float, 2, 0, 256, true, 9> DbF32;
 constexpr int64_t kLast64[] = {16384, 32768, 131072, 400000};
 constexpr int64_t kLast32[] = {32768, 700000};
 constexpr int kRowsPerSite = 12;
@@ -130,15 +133,17 @@ __device__ __forceinline__ void row_to_stage(u4 *st, int q, int lane, const floa
     }
 }
 
-template <class F>
+// kDa: form and store dA as well as dB's partials; without it b and da are not
+// touched. `steps` is the step count of the forms without one.
+template <class F, bool kDa>
 __global__ __launch_bounds__(kBwdThreads) void bwd_tiles(const u4 *__restrict__ a, const typename F::S *__restrict__ b,
                                                          const u4 *__restrict__ dc, u4 *__restrict__ da,
                                                          double *__restrict__ ws, uint32_t *__restrict__ counts,
-                                                         int64_t rows, int64_t groups)
+                                                         int64_t rows, int64_t groups, int steps)
 {
     typedef typename F::S S;
     constexpr int kSub = F::kSub;                     // 64-row tiles per step
-    constexpr int kSteps = F::kSteps;
+    const int nsteps = F::kSteps > 0 ? F::kSteps : steps;
     constexpr int CT = 64 * 6 * (int)sizeof(S) / 16;  // chunks per 64-row tile: 192 or 96
     constexpr int kStageBytes = 2 * 3 * 64 * 16;      // a and dC, 3 chunks per lane each
     constexpr int kRedBytes = 64 * 19 * 8;            // 18 accumulators per lane, padded
@@ -154,17 +159,17 @@ __global__ __launch_bounds__(kBwdThreads) void bwd_tiles(const u4 *__restrict__ 
     // this workgroup's tile group; its partial goes to slot grp
     const int64_t grp = blockIdx.x;
     // the wavefront's first 64-row tile t0; it takes t0 + D i for
-    // i < kSub * kSteps (D a multiple of 3)
-    constexpr int kPer = F::kTiles;
+    // i < kSub * nsteps (D a multiple of 3)
+    const int64_t per = (int64_t)kBwdWaves * kSub * nsteps;   // tiles of a workgroup
     int64_t t0, D;
     if constexpr (F::kBatch > 0) {
         constexpr int kB = F::kBatch;
         const int64_t bt = grp / kB, lam = grp - bt * kB;
         const int64_t nb = groups - bt * kB < kB ? groups - bt * kB : (int64_t)kB;
-        t0 = bt * kPer * kB + kBwdWaves * lam + wv;
+        t0 = bt * per * kB + kBwdWaves * lam + wv;
         D = kBwdWaves * nb;
     } else {
-        t0 = grp * kPer + wv;
+        t0 = grp * per + wv;
         D = kBwdWaves;
     }
     const int64_t nchunks = rows * 6 * (int64_t)sizeof(S) / 16;
@@ -192,21 +197,23 @@ __global__ __launch_bounds__(kBwdThreads) void bwd_tiles(const u4 *__restrict__ 
     // b before the first step: vector memory operations retire in order, so the
     // barrier that publishes b in LDS waits for the b load only while the step
     // is in flight.
-    const S bv = threadIdx.x < 72 ? b[threadIdx.x] : S(0);
+    const S bv = kDa && threadIdx.x < 72 ? b[threadIdx.x] : S(0);
     if (F::kEarly)
         load_step(t0);
-    if (threadIdx.x < 72)
-        bsh[threadIdx.x] = bv;
     if (blockIdx.x == 0 && threadIdx.x < 18)
         counts[threadIdx.x] = 0;   // for stage 2
-    __syncthreads();
-    const int pos = (int)((t0 * 64 + lane) % kRowsPerSite);   // row position in the site
-    const int j = pos / 3;                                     // its link
     S br[9], bi[9];
+    if constexpr (kDa) {
+        if (threadIdx.x < 72)
+            bsh[threadIdx.x] = bv;
+        __syncthreads();
+        const int pos = (int)((t0 * 64 + lane) % kRowsPerSite);   // row position in the site
+        const int j = pos / 3;                                     // its link
 #pragma unroll
-    for (int q = 0; q < 9; ++q) {
-        br[q] = bsh[2 * (9 * j + q)];
-        bi[q] = bsh[2 * (9 * j + q) + 1];
+        for (int q = 0; q < 9; ++q) {
+            br[q] = bsh[2 * (9 * j + q)];
+            bi[q] = bsh[2 * (9 * j + q) + 1];
+        }
     }
     double acc[18];
 #pragma unroll
@@ -214,7 +221,7 @@ __global__ __launch_bounds__(kBwdThreads) void bwd_tiles(const u4 *__restrict__ 
         acc[v] = 0.0;
     if (!F::kEarly)
         load_step(t0);
-    for (int k = 0; k < kSteps; ++k) {
+    for (int k = 0; k < nsteps; ++k) {
         const int64_t ts = t0 + D * kSub * k;   // the step's first tile
         if (ts * 64 >= rows)
             break;                              // wave-uniform
@@ -226,7 +233,7 @@ __global__ __launch_bounds__(kBwdThreads) void bwd_tiles(const u4 *__restrict__ 
             stg[192 + 64 * i + lane] = va[i];
         }
         wave_sync();
-        if (k + 1 < kSteps && (ts + D * kSub) * 64 < rows)
+        if (k + 1 < nsteps && (ts + D * kSub) * 64 < rows)
             load_step(ts + D * kSub);
         S o[kSub][6];
 #pragma unroll
@@ -236,7 +243,7 @@ __global__ __launch_bounds__(kBwdThreads) void bwd_tiles(const u4 *__restrict__ 
             row_from_stage(stg + 192, q, lane, x);
             // dA(k, m) = sum_l dC(k, l) conj(B(m, l))
 #pragma unroll
-            for (int m = 0; m < 3; ++m) {
+            for (int m = 0; kDa && m < 3; ++m) {
                 S re = 0, im = 0;
 #pragma unroll
                 for (int l = 0; l < 3; ++l)
@@ -258,6 +265,8 @@ __global__ __launch_bounds__(kBwdThreads) void bwd_tiles(const u4 *__restrict__ 
                          (double)g[2 * l], (double)g[2 * l + 1]);
         }
         wave_sync();
+        if constexpr (!kDa)
+            continue;
 #pragma unroll
         for (int q = 0; q < kSub; ++q)
             row_to_stage(stg, q, lane, o[q]);
@@ -339,7 +348,9 @@ __global__ __launch_bounds__(kBwdThreads) void bwd_tiles(const u4 *__restrict__ 
 // back the XCD's whole L2 in every workgroup, which made one launch slower
 // than two. Two launches took 9.3 us (4.7 and 4.6) after stage 1 in FP64, at
 // L = 32 and at 24^4 alike; this one takes 5.8 and 5.4.
-__global__ __launch_bounds__(kChunkThreads) void bwd_sum(double *__restrict__ ws, double *__restrict__ db,
+// T: the type dB is stored in, double, or float for the FP64 sum rounded once.
+template <typename T>
+__global__ __launch_bounds__(kChunkThreads) void bwd_sum(double *__restrict__ ws, T *__restrict__ db,
                                                          uint32_t *__restrict__ counts, int64_t groups,
                                                          int64_t chunks)
 {
@@ -387,7 +398,7 @@ __global__ __launch_bounds__(kChunkThreads) void bwd_sum(double *__restrict__ ws
     }
     if (chunks == 1) {
         if (threadIdx.x < 4)
-            db[4 * u + threadIdx.x] = total;
+            db[4 * u + threadIdx.x] = (T)total;
         return;
     }
     if (wv == 0) {
@@ -407,14 +418,15 @@ __global__ __launch_bounds__(kChunkThreads) void bwd_sum(double *__restrict__ ws
     for (int w = 32; w > 0; w >>= 1)
         x += __shfl_down(x, w, 64);
     if (lane == 0)
-        db[4 * u + wv] = x;
+        db[4 * u + wv] = (T)x;
 }
 
 // dB of an empty lattice.
-__global__ __launch_bounds__(128) void bwd_zero(double *__restrict__ db)
+template <typename T>
+__global__ __launch_bounds__(128) void bwd_zero(T *__restrict__ db)
 {
     if (threadIdx.x < 72)
-        db[threadIdx.x] = 0.0;
+        db[threadIdx.x] = T(0);
 }
 
 // The 64-row tiles of one workgroup of stage 1 for a lattice of n sites.
@@ -437,6 +449,21 @@ int64_t bwd_groups(int64_t sites, int precision)
 
 static int64_t bwd_chunks(int64_t groups) { return (groups + kChunk - 1) / kChunk; }
 
+// Steps of dB alone: nothing is written per site, so long-lived workgroups
+// cost nothing and save closing reductions and partials. About 512
+// workgroups, two per CU, of at most 32 steps (microseconds, both stages,
+// against the steps of the whole adjoint): FP64 131,072 sites 27 / 30,
+// 331,776 63 / 70, 2^20 182 / 218 (6.6 TB/s), 2,560,000 448 / 538; FP32 2^20 96
+// / 111. Fewer or more workgroups at mid-sized lattices and caps of 12 or 15
+// were 0-3% slower.
+static int db_steps(int64_t sites, int precision)
+{
+    const int64_t tiles = (sites * kRowsPerSite + 63) / 64;
+    const int64_t per_step = kBwdWaves * (precision == 0 ? DbF64::kSub : DbF32::kSub);
+    const int64_t steps = (tiles + 512 * per_step - 1) / (512 * per_step);
+    return (int)(steps < 32 ? steps : 32);
+}
+
 // The partials, and as many doubles as there are run sums: stage 2 keeps its
 // 18 counts (4 bytes each) there. A form with fewer steps makes more groups,
 // so the groups do not grow with the sites everywhere; the workspace does, and
@@ -458,40 +485,68 @@ int64_t bwd_workspace_doubles(int64_t sites, int precision)
 
 int bwd_block_threads() { return kBwdThreads; }
 
-template <class F>
+template <class F, bool kDa>
 static hipError_t launch_tiles_f(const void *a, const void *b, const void *dc, void *da, int64_t sites, double *ws,
-                                 uint32_t *counts, int64_t groups, hipStream_t s)
+                                 uint32_t *counts, int64_t groups, int steps, hipStream_t s)
 {
     static PadCache cache;
     const LaunchPlan plan =
-        launch_plan(reinterpret_cast<const void *>(bwd_tiles<F>), F::kWaves, kBwdThreads, groups, cache);
-    return launch_k(bwd_tiles<F>, dim3((unsigned)groups), dim3(kBwdThreads), s, plan.pad, (const u4 *)a,
-                    (const typename F::S *)b, (const u4 *)dc, (u4 *)da, ws, counts, sites * kRowsPerSite, groups);
+        launch_plan(reinterpret_cast<const void *>(bwd_tiles<F, kDa>), F::kWaves, kBwdThreads, groups, cache);
+    return launch_k(bwd_tiles<F, kDa>, dim3((unsigned)groups), dim3(kBwdThreads), s, plan.pad, (const u4 *)a,
+                    (const typename F::S *)b, (const u4 *)dc, (u4 *)da, ws, counts, sites * kRowsPerSite, groups, steps);
 }
 
-hipError_t launch_bwd(const void *a, const void *b, const void *dc, void *da, double *db, int64_t sites,
+// Stage 2 over `groups` partials; db in double, or in float for `db_float`.
+static hipError_t launch_sum(double *ws, uint32_t *counts, int64_t groups, void *db, bool db_float, hipStream_t s)
+{
+    const int64_t chunks = bwd_chunks(groups);
+    const dim3 grid((unsigned)chunks, 18);
+    if (db_float)
+        return launch_k(bwd_sum<float>, grid, dim3(kChunkThreads), s, 0, ws, (float *)db, counts, groups, chunks);
+    return launch_k(bwd_sum<double>, grid, dim3(kChunkThreads), s, 0, ws, (double *)db, counts, groups, chunks);
+}
+
+hipError_t launch_bwd(const void *a, const void *b, const void *dc, void *da, void *db, bool db_float, int64_t sites,
                       int precision, double *ws, hipStream_t s)
 {
-    const int64_t groups = bwd_groups(sites, precision), chunks = bwd_chunks(groups);
-    const int64_t per = tiles_per_group(sites, precision);
+    const int64_t groups = bwd_groups(sites, precision), per = tiles_per_group(sites, precision);
     uint32_t *counts = reinterpret_cast<uint32_t *>(ws + 72 * groups);
     hipError_t e;
     if (precision == 0)
-        e = (per == BwdF64x1::kTiles   ? launch_tiles_f<BwdF64x1>
-             : per == BwdF64x2::kTiles ? launch_tiles_f<BwdF64x2>
-                                       : launch_tiles_f<BwdF64x4>)(a, b, dc, da, sites, ws, counts, groups, s);
+        e = (per == BwdF64x1::kTiles   ? launch_tiles_f<BwdF64x1, true>
+             : per == BwdF64x2::kTiles ? launch_tiles_f<BwdF64x2, true>
+                                       : launch_tiles_f<BwdF64x4, true>)(a, b, dc, da, sites, ws, counts, groups, 0, s);
     else
-        e = (per == BwdF32x1::kTiles    ? launch_tiles_f<BwdF32x1>
-             : sites <= kLast32[1] ? launch_tiles_f<BwdF32x2>
-                                        : launch_tiles_f<BwdF32Large>)(a, b, dc, da, sites, ws, counts, groups, s);
-    if (e != hipSuccess)
-        return e;
-    return launch_k(bwd_sum, dim3((unsigned)chunks, 18), dim3(kChunkThreads), s, 0, ws, db, counts, groups, chunks);
+        e = (per == BwdF32x1::kTiles    ? launch_tiles_f<BwdF32x1, true>
+             : sites <= kLast32[1] ? launch_tiles_f<BwdF32x2, true>
+                                        : launch_tiles_f<BwdF32Large, true>)(a, b, dc, da, sites, ws, counts, groups, 0,
+                                                                             s);
+    return e != hipSuccess ? e : launch_sum(ws, counts, groups, db, db_float, s);
+}
+
+// Its groups are never more than those of the whole adjoint, whose workspace
+// therefore serves it.
+hipError_t launch_db(const void *a, const void *dc, void *db, bool db_float, int64_t sites, int precision, double *ws,
+                     hipStream_t s)
+{
+    const int steps = db_steps(sites, precision);
+    const int64_t tiles = (sites * kRowsPerSite + 63) / 64;
+    const int64_t per = (int64_t)kBwdWaves * (precision == 0 ? DbF64::kSub : DbF32::kSub) * steps;
+    const int64_t groups = (tiles + per - 1) / per;
+    uint32_t *counts = reinterpret_cast<uint32_t *>(ws + 72 * groups);
+    const hipError_t e = (precision == 0 ? launch_tiles_f<DbF64, false> : launch_tiles_f<DbF32, false>)(
+        a, nullptr, dc, nullptr, sites, ws, counts, groups, steps, s);
+    return e != hipSuccess ? e : launch_sum(ws, counts, groups, db, db_float, s);
 }
 
 // An empty lattice has dB = 0 (a kernel rather than a memset, so the call is
 // safe to capture).
-hipError_t launch_bwd_zero(double *db, hipStream_t s) { return launch_k(bwd_zero, dim3(1), dim3(128), s, 0, db); }
+hipError_t launch_bwd_zero(void *db, bool db_float, hipStream_t s)
+{
+    if (db_float)
+        return launch_k(bwd_zero<float>, dim3(1), dim3(128), s, 0, (float *)db);
+    return launch_k(bwd_zero<double>, dim3(1), dim3(128), s, 0, (double *)db);
+}
 
 // ---- the library-owned workspace of su3_mult_nn_bwd_noalloc ---------------
 // A fixed device array (each device the library runs on holds its own copy

@@ -238,13 +238,17 @@ hipError_t launch_stream_shape(const void *a, const void *b, void *c, int64_t ti
                                int waves_per_cu, int tile_order, hipStream_t s);
 // Adjoint: stage 1 writes per-workgroup partial sums of db into ws (72 x
 // bwd_groups doubles, in 32-byte quads of components), stage 2 reduces them
-// in a fixed order; bwd_workspace_doubles is the workspace of both.
+// in a fixed order; bwd_workspace_doubles is the workspace of both. db is
+// stored in double, or in float (rounded once) for db_float. launch_db forms
+// db alone.
 int64_t bwd_groups(int64_t sites, int precision);
 int64_t bwd_workspace_doubles(int64_t sites, int precision);
 int bwd_block_threads();
-hipError_t launch_bwd(const void *a, const void *b, const void *dc, void *da, double *db, int64_t sites,
+hipError_t launch_bwd(const void *a, const void *b, const void *dc, void *da, void *db, bool db_float, int64_t sites,
                       int precision, double *ws, hipStream_t s);
-hipError_t launch_bwd_zero(double *db, hipStream_t s);
+hipError_t launch_db(const void *a, const void *dc, void *db, bool db_float, int64_t sites, int precision, double *ws,
+                     hipStream_t s);
+hipError_t launch_bwd_zero(void *db, bool db_float, hipStream_t s);
 // Bytes of the library-owned adjoint workspace (one static device array per
 // device) and its device address on the current device, looked up on the
 // first call per device.

@@ -345,8 +345,8 @@ def launch_shape(sites: int, form: int, device: torch.device | int | None = None
 class SU3MultNN(torch.autograd.Function):
     """c = a @ b[j] per site and link, differentiable in a and b (FP64, FP32).
 
-    backward uses the library's fused adjoint: da = dc b^H and a deterministic
-    FP64 site sum for db, returned in b's dtype."""
+    backward forms what is asked for: da = dc b^H and, with it or alone, a
+    deterministic FP64 site sum for db, rounded once to b's dtype."""
 
     @staticmethod
     def forward(ctx, a, b):
@@ -359,9 +359,25 @@ class SU3MultNN(torch.autograd.Function):
         a, b = ctx.saved_tensors
         # autograd may hand over a lazy conjugate view (after a .conj() in
         # the graph); the kernels need the values themselves
-        da, db = mult_nn_bwd(a, b, dc.resolve_conj().resolve_neg().contiguous())
-        return (da if ctx.needs_input_grad[0] else None,
-                db.to(b.dtype) if ctx.needs_input_grad[1] else None)
+        dc = dc.resolve_conj().resolve_neg().contiguous()
+        form = form_of(a)
+        if form not in (SU3_F64, SU3_F32):
+            raise ValueError("the adjoint exists for FP64 and FP32")
+        need_a, need_b = ctx.needs_input_grad
+        if not need_b:
+            return (mult_na(dc, b) if need_a else None), None
+        if dc.dtype != a.dtype or dc.shape != a.shape:
+            raise ValueError("dc must match a in dtype and shape")
+        _check_b(b, form)
+        da = torch.empty_like(a) if need_a else None
+        db = torch.empty((4, 3, 3), dtype=b.dtype, device=a.device)
+        ws = mult_nn_bwd_workspace(a.shape[0], form, a.device)
+        _need_gpu(a, b, dc, db, ws)
+        with torch.cuda.device(a.device):
+            check(abi.su3_mult_nn_grad(a.data_ptr(), b.data_ptr(), dc.data_ptr(), da.data_ptr() if need_a else None,
+                                       db.data_ptr(), a.shape[0], form, ws.data_ptr(), ws.numel(), _stream(a)),
+                  "su3_mult_nn_grad")
+        return da, db
 
 
 def mult_nn_autograd(a: torch.Tensor, b: torch.Tensor) -> torch.Tensor:

@@ -77,6 +77,18 @@ __device__ __forceinline__ int64_t xcd_order(int64_t bid, int64_t nb)
     return x * q + (x < r ? x : r) + bid / kXcds;
 }
 
+// Grouped tile order: within every 64 tiles each XCD takes 8 consecutive ones,
+// so that its runs on a plane join up while the whole grid still walks the
+// array in order. A bijection on [0, nb): the tail of less than 64 keeps the
+// index.
+__device__ __forceinline__ int64_t group_order(int64_t bid, int64_t nb)
+{
+    constexpr int kGroup = 8, kSpan = kXcds * kGroup;
+    const int64_t k = bid / kSpan;
+    const int r = (int)(bid - k * kSpan);
+    return (k + 1) * kSpan > nb ? bid : k * kSpan + r % kXcds * kGroup + r / kXcds;
+}
+
 // The tile of this workgroup in the site-major products, the matrix-vector
 // product and the reconstruct-12 pack and unpack: XCD-contiguous (at L = 48
 // it streams 3-5% faster than tile = workgroup index at the best cap of

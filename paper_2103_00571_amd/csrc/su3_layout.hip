@@ -118,14 +118,20 @@ __global__ __launch_bounds__(kBlock) void transpose_aos_soa(const V *__restrict_
 }
 
 // The same transforms for the larger lattices, one tile of TS sites per
-// workgroup of B threads, tile = workgroup index. What bounds them is the 36
-// plane streams: a kernel that only copies the same addresses (36 KiB per
-// workgroup in and out, no LDS) peaks at 6.0 (to planes) and 6.2 TB/s (from
-// planes) at 2,560,000 FP64 sites, with one such workgroup per CU, and falls
-// to 5.6 and 5.9 with two to four; the run length on the planes (1 to 16 KiB)
-// does not matter. So the tile and the number of resident workgroups set the
-// bytes in flight, and many threads with few elements each keep a tile's
-// life short. launch_aos_soa states which tile serves which size.
+// workgroup of B threads. What bounds them is the 36 plane streams: a kernel
+// that only copies the same addresses (36 KiB per workgroup in and out, no
+// LDS, nontemporal) peaks at 6.0 (to planes) and 6.2 TB/s (from planes) at
+// 2,560,000 FP64 sites, with one such workgroup per CU, and falls to 5.6 and
+// 5.9 with two to four; the run length on the planes (1 to 16 KiB) does not
+// matter. So the tile and the number of resident workgroups set the bytes in
+// flight, and many threads with few elements each keep a tile's life short.
+// launch_aos_soa states which tile serves which size.
+// kThrough: write-through stores (OutWindow) instead of nontemporal ones; from
+// planes also the grouped tile order (group_order), which alone is worth 1-2%
+// and with these stores 4-5% (groups of 2 to 64 and all the tiles of an XCD
+// together were tried). To planes the groups collide where the plane stride is
+// a power of two (2^17 and 2^19 sites: 0.84 to 0.93 of the speed) and gain 1%
+// elsewhere, so workgroups take their tiles in order.
 //
 // kHalo, for planes that do not start on 128-byte lines (a site count that
 // is no multiple of 8 in FP64 or 16 in FP32, dense): a run cut at the tile's
@@ -136,7 +142,7 @@ __global__ __launch_bounds__(kBlock) void transpose_aos_soa(const V *__restrict_
 // one line's worth of sites past its tile and moves each plane's window up to
 // that plane's next line boundary, so that every line is written whole by one
 // workgroup; the first tile also writes the sites before its window.
-template <typename V, int TS, int B, bool kHalo>
+template <typename V, int TS, int B, bool kHalo, bool kThrough>
 __global__ __launch_bounds__(B) void to_soa_tile(const V *__restrict__ src, V *__restrict__ dst, int64_t n,
                                                  int64_t pitch)
 {
@@ -171,12 +177,17 @@ __global__ __launch_bounds__(B) void to_soa_tile(const V *__restrict__ src, V *_
         const int e = threadIdx.x + i * B, p = e / TS;
         o[i] = tile[p][e % TS + shift(p)];
     }
+    const OutWindow out = out_window(dst, 36 * pitch * (int64_t)sizeof(V));   // kThrough: below 4 GiB
 #pragma unroll
     for (int i = 0; i < kOut; ++i) {
         const int e = threadIdx.x + i * B, p = e / TS;
         const int64_t s = s0 + e % TS + shift(p);
-        if (s < n)
+        if constexpr (kThrough) {
+            if (s < n)
+                st_out<true>(out, ((uint32_t)p * (uint32_t)pitch + (uint32_t)s) * (uint32_t)sizeof(V), o[i]);
+        } else if (s < n) {
             st_stream(dst + (int64_t)p * pitch + s, o[i]);
+        }
     }
     if (kHalo && blockIdx.x == 0) {
         for (int e = threadIdx.x; e < 36 * H; e += B) {
@@ -189,14 +200,15 @@ __global__ __launch_bounds__(B) void to_soa_tile(const V *__restrict__ src, V *_
 
 // kNt: nontemporal plane loads. Where planes do not start on lines, two
 // workgroups read the line at a tile's edge, and FP32 keeps it in the cache.
-template <typename V, int TS, int B, bool kNt>
+template <typename V, int TS, int B, bool kNt, bool kThrough>
 __global__ __launch_bounds__(B) void to_aos_tile(const V *__restrict__ src, V *__restrict__ dst, int64_t n,
                                                  int64_t pitch)
 {
     constexpr int kPer = 36 * TS / B;
     static_assert(kPer * B == 36 * TS, "a tile splits evenly over the workgroup");
     __shared__ V tile[36][TS + 1];
-    const int64_t s0 = (int64_t)blockIdx.x * TS, nout = n * 36;
+    const int64_t t = kThrough ? group_order(blockIdx.x, gridDim.x) : (int64_t)blockIdx.x;
+    const int64_t s0 = t * TS, nout = n * 36;
     V v[kPer];
 #pragma unroll
     for (int i = 0; i < kPer; ++i) {
@@ -216,12 +228,10 @@ __global__ __launch_bounds__(B) void to_aos_tile(const V *__restrict__ src, V *_
         const int e = threadIdx.x + i * B;
         v[i] = tile[e % 36][e / 36];
     }
+    const OutWindow out = out_window(dst + s0 * 36, (nout - s0 * 36) * (int64_t)sizeof(V));
 #pragma unroll
-    for (int i = 0; i < kPer; ++i) {
-        const int64_t g = s0 * 36 + threadIdx.x + i * B;
-        if (g < nout)
-            st_stream(dst + g, v[i]);
-    }
+    for (int i = 0; i < kPer; ++i)
+        st_out<kThrough>(out, (uint32_t)((threadIdx.x + i * B) * sizeof(V)), v[i]);
 }
 
 // FP32 with both sides in 16-byte accesses: two elements of a site on the
@@ -570,15 +580,15 @@ static hipError_t launch_tiles(const VS *src, VD *dst, int64_t n, int64_t pitch,
     const LaunchPlan plan = launch_plan(reinterpret_cast<const void *>(K), kPerCU * (B / 64), B, grid, cache);
     return launch_k(K, dim3((unsigned)grid), dim3(B), s, plan.pad, src, dst, n, pitch);
 }
-template <typename V, int TS, int B, bool kHalo, int kPerCU>
+template <typename V, int TS, int B, bool kHalo, bool kThrough, int kPerCU>
 static hipError_t launch_to_soa(const void *src, void *dst, int64_t n, int64_t pitch, hipStream_t s)
 {
-    return launch_tiles<to_soa_tile<V, TS, B, kHalo>, TS, B, kPerCU>((const V *)src, (V *)dst, n, pitch, s);
+    return launch_tiles<to_soa_tile<V, TS, B, kHalo, kThrough>, TS, B, kPerCU>((const V *)src, (V *)dst, n, pitch, s);
 }
-template <typename V, int TS, int B, bool kNt, int kPerCU>
+template <typename V, int TS, int B, bool kNt, bool kThrough, int kPerCU>
 static hipError_t launch_to_aos(const void *src, void *dst, int64_t n, int64_t pitch, hipStream_t s)
 {
-    return launch_tiles<to_aos_tile<V, TS, B, kNt>, TS, B, kPerCU>((const V *)src, (V *)dst, n, pitch, s);
+    return launch_tiles<to_aos_tile<V, TS, B, kNt, kThrough>, TS, B, kPerCU>((const V *)src, (V *)dst, n, pitch, s);
 }
 // The general path: any size, a grid of 64-site tiles that loops past kOnePass.
 template <typename V, bool kXcd>
@@ -596,28 +606,38 @@ static hipError_t launch_general(const void *src, void *dst, int64_t n, int64_t 
 //  FP64, up to 49,152 sites: the general path; its 64-site tiles give more CUs
 //    work than larger ones, and its XCD order collides less at 2^15 sites.
 //  FP64 to planes, on lines: up to 65,536 sites 128-site tiles, the whole grid
-//    resident at two per CU (65,536: 13.3 / 15.6); above, 32-site tiles of
-//    576 threads (24^4: 64 / 78, 40^4: 500 / 565, 48^4: 1054 / 1150; 1.05 to
-//    1.21 times as fast at 20 sizes and pitches). Off lines, 128-site tiles with
-//    the halo, two per CU up to 131,072 sites (65,537: 13.5 / 15.9) and one
+//    resident at two per CU (65,536: 13.3 / 15.6); above, 32-site tiles: up to
+//    262,144 sites 384 threads, three per CU, write-through (81,920: 17.0,
+//    160,000: 30.4, 230,400: 46.8; 1.00 to 1.17 times the next form at 8
+//    sizes, dense and padded), beyond that 576 threads, nontemporal (24^4: 64 /
+//    78, 40^4: 480 / 565, 48^4: 1054 / 1150; the form before it is level
+//    there and 5% slower at 2^20). Off lines, 128-site tiles with the
+//    halo, two per CU up to 131,072 sites (65,537: 13.5 / 15.9) and one
 //    above (31^4: 193 / 250, 2,560,001: 533 / 630).
-//  FP64 from planes, on lines: up to 65,536 sites as above; up to 196,608
-//    32-site tiles (160,000: 32.4 / 35.2); above, 128-site tiles, one per CU
-//    (24^4: 64 / 72, 40^4: 478 / 523, 48^4: 996 / 1074; 1.03 to 1.15 at 20
-//    sizes and pitches), whose last generation of workgroups costs too much
-//    on fewer tiles. Off lines the general path up to 196,608 sites and these
-//    tiles above (31^4: 177 / 208).
-//  FP32 on lines: pairs; 64-site tiles of 128 threads up to 131,072 sites
-//    (65,536: 7.2 / 10.5); above, 576 threads on 64 sites to planes (40^4: 243
-//    / 257, 48^4: 516 / 558; 1.02 to 1.10 at 20 sizes and pitches). From
-//    planes, 128-site pairs where the plane stride is a multiple of 4 MiB
-//    and the planes collide (2^20: 97 / 105, 1.08 to 1.10) and single
-//    elements on 64-site tiles of 768 threads elsewhere (1.00 to 1.05; pairs
-//    lost up to 3% there).
+//  FP64 from planes, on lines: up to 65,536 sites as above; beyond, 32-site
+//    tiles of 384 threads, three per CU, grouped and write-through (160,000:
+//    30.1 / 35.2, 24^4: 60.4 / 72, 40^4: 472 / 523). Against 128-site tiles in
+//    order with nontemporal stores, the former choice there: 1.02 to 1.15 at
+//    14 sizes, dense and padded, and 0.97 at one (230,400 padded). Off lines
+//    the general path up to 196,608 sites and 128-site tiles above, one per CU,
+//    also grouped and write-through (31^4: 175 / 208; 0.99 to 1.10 times
+//    the tiles in order at 7 sizes).
+//  FP32 on lines: pairs on 64-site tiles of 128 threads up to 131,072 sites
+//    (65,536: 7.2 / 10.5). Above, to planes, single elements on 64-site tiles
+//    of 256 threads, three per CU, write-through, up to 400,000 sites (230,400:
+//    24.9, 24^4: 32.6; 0.98 to 1.25 times the next form) and pairs on 64-site
+//    tiles of 576 threads beyond (40^4: 234 / 257, 48^4: 516 / 558; the form
+//    before it is level there and 3% slower at 2^20 and 2^21). From planes,
+//    64-site tiles of 768 threads, grouped and write-through (160,000: 17.4,
+//    24^4: 32.4, 40^4: 232 / 250; 1.00 to 1.14 times the same tiles in order
+//    with nontemporal stores).
 //  FP32 off lines: up to 49,152 sites the general path; above, 128-site tiles
 //    of 256 threads, to planes with the halo, two per CU (65,537: 9.3 / 10.7,
 //    31^4: 105 / 142, 2,560,001: 266 / 381), from planes with cached loads
 //    (65,537: 8.6 / 11.1, 31^4: 94 / 105, 2,560,001: 251 / 280).
+//  Write-through stores to planes take 32-bit offsets from the first plane, so
+//    those forms need all planes within 4 GiB: pitches of at most 7 * 2^20
+//    (longer ones, far beyond those sizes, take the nontemporal form).
 //  Over 2^27 sites, where a one-pass grid could pass 2^32 threads: the general
 //    path, which loops.
 hipError_t launch_aos_soa(const void *src, void *dst, int64_t sites, int64_t pitch, int elem_bytes, bool to_soa,
@@ -625,34 +645,33 @@ hipError_t launch_aos_soa(const void *src, void *dst, int64_t sites, int64_t pit
 {
     const int64_t n = sites;
     const bool lines = pitch * elem_bytes % 128 == 0 && (uintptr_t)(to_soa ? dst : src) % 128 == 0;
-    const bool huge = n > (int64_t)1 << 27;
+    const bool huge = n > (int64_t)1 << 27, window = pitch <= (int64_t)7 << 20;
     if (elem_bytes == 16) {
         if (n <= 49152 || huge || (!to_soa && !lines && n <= 196608))
             return launch_general<d2, true>(src, dst, n, pitch, to_soa, s);
         if (to_soa && !lines)
-            return n <= 131072 ? launch_to_soa<d2, 128, 768, true, 0>(src, dst, n, pitch, s)
-                               : launch_to_soa<d2, 128, 768, true, 1>(src, dst, n, pitch, s);
+            return n <= 131072 ? launch_to_soa<d2, 128, 768, true, false, 0>(src, dst, n, pitch, s)
+                               : launch_to_soa<d2, 128, 768, true, false, 1>(src, dst, n, pitch, s);
         if (to_soa)
-            return n <= 65536 ? launch_to_soa<d2, 128, 768, false, 0>(src, dst, n, pitch, s)
-                              : launch_to_soa<d2, 32, 576, false, 0>(src, dst, n, pitch, s);
-        if (n <= 65536)
-            return launch_to_aos<d2, 128, 768, true, 0>(src, dst, n, pitch, s);
-        return n <= 196608 ? launch_to_aos<d2, 32, 576, true, 0>(src, dst, n, pitch, s)
-                           : launch_to_aos<d2, 128, 768, true, 1>(src, dst, n, pitch, s);
+            return n <= 65536              ? launch_to_soa<d2, 128, 768, false, false, 0>(src, dst, n, pitch, s)
+                   : n <= 262144 && window ? launch_to_soa<d2, 32, 384, false, true, 3>(src, dst, n, pitch, s)
+                                           : launch_to_soa<d2, 32, 576, false, false, 0>(src, dst, n, pitch, s);
+        return n <= 65536 ? launch_to_aos<d2, 128, 768, true, false, 0>(src, dst, n, pitch, s)
+               : lines    ? launch_to_aos<d2, 32, 384, true, true, 3>(src, dst, n, pitch, s)
+                          : launch_to_aos<d2, 128, 768, true, true, 1>(src, dst, n, pitch, s);
     }
     if (huge || (!lines && n <= 49152))
         return launch_general<f2, false>(src, dst, n, pitch, to_soa, s);
     if (!lines)
-        return to_soa ? launch_to_soa<f2, 128, 256, true, 2>(src, dst, n, pitch, s)
-                      : launch_to_aos<f2, 128, 256, false, 0>(src, dst, n, pitch, s);
+        return to_soa ? launch_to_soa<f2, 128, 256, true, false, 2>(src, dst, n, pitch, s)
+                      : launch_to_aos<f2, 128, 256, false, false, 0>(src, dst, n, pitch, s);
     if (n <= 131072)
         return to_soa ? launch_tiles<to_soa_pairs<64, 128>, 64, 128, 0>((const f4 *)src, (f2 *)dst, n, pitch, s)
                       : launch_tiles<to_aos_pairs<64, 128>, 64, 128, 0>((const f2 *)src, (f4 *)dst, n, pitch, s);
-    if (to_soa)
-        return launch_tiles<to_soa_pairs<64, 576>, 64, 576, 0>((const f4 *)src, (f2 *)dst, n, pitch, s);
-    return pitch * 8 % ((int64_t)4 << 20) == 0
-               ? launch_tiles<to_aos_pairs<128, 576>, 128, 576, 0>((const f2 *)src, (f4 *)dst, n, pitch, s)
-               : launch_to_aos<f2, 64, 768, true, 0>(src, dst, n, pitch, s);
+    if (!to_soa)
+        return launch_to_aos<f2, 64, 768, true, true, 0>(src, dst, n, pitch, s);
+    return n <= 400000 && window ? launch_to_soa<f2, 64, 256, false, true, 3>(src, dst, n, pitch, s)
+                                 : launch_tiles<to_soa_pairs<64, 576>, 64, 576, 0>((const f4 *)src, (f2 *)dst, n, pitch, s);
 }
 
 hipError_t launch_stream_copy(const void *src, void *dst, int64_t bytes, hipStream_t s)

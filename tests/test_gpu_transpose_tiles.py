@@ -48,3 +48,32 @@ def test_transforms_at_the_edges(sites, dtype, offset):
         torch.cuda.synchronize()
         assert torch.equal(back[1:sites + 1], x)
         assert bool(torch.isnan(back[0].real).all()) and bool(torch.isnan(back[-1].real).all())
+
+
+# Both sides of the sizes where the write-through forms begin and end, and a
+# tail of tiles shorter than one group of the tile order.
+@pytest.mark.parametrize("dtype", [torch.complex128, torch.complex64])
+@pytest.mark.parametrize("sites", [65552, 131104, 200000, 262144, 262160, 400000, 400016, 525328])
+def test_grouped_and_write_through_tiles(sites, dtype):
+    test_transforms_at_the_edges(sites, dtype, 0)
+
+
+# Planes that span more than the 4 GiB that a 32-bit offset reaches.
+@pytest.mark.parametrize("dtype", [torch.complex128, torch.complex64])
+@pytest.mark.parametrize("pitch", [7 << 20, (7 << 20) + 16, (15 << 20) + 16])
+def test_long_plane_strides(pitch, dtype):
+    from paper_2103_00571_amd import abi
+
+    form, sites = (abi.SU3_F64 if dtype == torch.complex128 else abi.SU3_F32), 140000
+    say("transpose sites=%d pitch=%d %s" % (sites, pitch, dtype))
+    x = torch.randn((sites, 36), dtype=dtype, device=dev())
+    planes = torch.zeros((36, pitch), dtype=dtype, device=dev())
+    stream = torch.cuda.current_stream().cuda_stream
+    assert abi.su3_aos_to_soa_pitched(x.data_ptr(), planes.data_ptr(), sites, pitch, form, stream) == 0
+    torch.cuda.synchronize()
+    assert torch.equal(planes[:, :sites], x.t())
+    assert int(torch.count_nonzero(planes[:, sites:])) == 0
+    back = torch.empty_like(x)
+    assert abi.su3_soa_to_aos_pitched(planes.data_ptr(), back.data_ptr(), sites, pitch, form, stream) == 0
+    torch.cuda.synchronize()
+    assert torch.equal(back, x)

@@ -44,18 +44,12 @@
 #ifndef SU3_WAVES_BF16
 #define SU3_WAVES_BF16 14
 #endif
-#ifndef SU3_WAVES_R12
-#define SU3_WAVES_R12 6
-#endif
-// (R12C: 3 KiB of loads per wavefront, like FP64; R12F64: 6 KiB; AN: 9 KiB.)
+// R12C: 3 KiB of loads per wavefront, like FP64; R12F64: 6 KiB.
 #ifndef SU3_WAVES_R12C
 #define SU3_WAVES_R12C 13
 #endif
 #ifndef SU3_WAVES_R12F64
 #define SU3_WAVES_R12F64 6
-#endif
-#ifndef SU3_WAVES_AN
-#define SU3_WAVES_AN 6
 #endif
 #ifndef SU3_WAVES_SOA_F64
 #define SU3_WAVES_SOA_F64 8
@@ -69,6 +63,13 @@
 #endif
 
 namespace su3 {
+
+// FP32 reconstruct-12, 6 KiB of loads per wavefront: 200,000 sites 16.5 us with
+// 8 and 17.0 with 6, 2,560,000 sites 200 with 8 and 193 with 6.
+constexpr WaveCaps kCapsR12 = {{200000000, INT64_MAX}, {8, 6, 6}};
+// a^H b: FP64 100,000 sites 18.7 us with 6 and 19.9 with 4, 2,560,000 sites 462
+// with 6 and 452 with 4 (FP32 231 and 227).
+constexpr WaveCaps kCapsAn = {{600000000, INT64_MAX}, {6, 4, 4}};
 
 constexpr int kAosBlock = SU3_AOS_BLOCK;
 // Threads per workgroup of fwd_soa: 128 measured 3% faster than 256 for FP64
@@ -146,7 +147,8 @@ __device__ __forceinline__ void pack_chunks(const S *x, u4 (&v)[N])
 
 // FP64: unit = output row k of link j (pos = 3j + k); 48 B in, 48 B out.
 struct FormF64 {
-    static constexpr int kIn = 3, kOut = 3, kUnitsPerSite = 12, kWavesPerCU = SU3_WAVES_F64;
+    static constexpr int kIn = 3, kOut = 3, kUnitsPerSite = 12;
+    static constexpr WaveCaps kCaps = one_cap(SU3_WAVES_F64);
     typedef double B;
     typedef Link<double> Coef;
     __device__ static void load(const B *b, int pos, Coef &m) { load_link(b, pos / 3, m); }
@@ -162,7 +164,8 @@ struct FormF64 {
 // FP32: unit = rows 2w and 2w+1 of a site (w = 0..5), which may belong to two
 // links; 48 B in, 48 B out.
 struct FormF32 {
-    static constexpr int kIn = 3, kOut = 3, kUnitsPerSite = 6, kWavesPerCU = SU3_WAVES_F32;
+    static constexpr int kIn = 3, kOut = 3, kUnitsPerSite = 6;
+    static constexpr WaveCaps kCaps = one_cap(SU3_WAVES_F32);
     typedef float B;
     struct Coef {
         Link<float> m[2];
@@ -185,7 +188,8 @@ struct FormF32 {
 // BF16 storage, FP32 arithmetic: unit = rows 4w .. 4w+3 (w = 0..2); row i
 // uses link (4w + i) / 3; 48 B in, 48 B out, rounded to nearest even.
 struct FormBF16 {
-    static constexpr int kIn = 3, kOut = 3, kUnitsPerSite = 3, kWavesPerCU = SU3_WAVES_BF16;
+    static constexpr int kIn = 3, kOut = 3, kUnitsPerSite = 3;
+    static constexpr WaveCaps kCaps = one_cap(SU3_WAVES_BF16);
     typedef float B;
     struct Coef {
         Link<float> m[4];
@@ -239,7 +243,8 @@ __device__ __forceinline__ void recon_row2_f32(const float *r0, const float *r1,
 // Reconstruct-12: unit = links 2w, 2w+1 (w = 0, 1); rows 0-1 of each in FP32
 // (96 B in), the full FP32 products out (144 B).
 struct FormR12 {
-    static constexpr int kIn = 6, kOut = 9, kUnitsPerSite = 2, kWavesPerCU = SU3_WAVES_R12;
+    static constexpr int kIn = 6, kOut = 9, kUnitsPerSite = 2;
+    static constexpr WaveCaps kCaps = kCapsR12;
     typedef float B;
     struct Coef {
         Link<float> m[2];
@@ -272,7 +277,8 @@ struct FormR12 {
 // and rows 0-1 of the product out (48 B). Rows 0-1 of a*b depend only on
 // rows 0-1 of a, so no row is rebuilt.
 struct FormR12C {
-    static constexpr int kIn = 3, kOut = 3, kUnitsPerSite = 4, kWavesPerCU = SU3_WAVES_R12C;
+    static constexpr int kIn = 3, kOut = 3, kUnitsPerSite = 4;
+    static constexpr WaveCaps kCaps = one_cap(SU3_WAVES_R12C);
     typedef float B;
     typedef Link<float> Coef;
     __device__ static void load(const B *b, int pos, Coef &m) { load_link(b, pos, m); }
@@ -308,7 +314,8 @@ __device__ __forceinline__ void recon_row2_f64(const double *r0, const double *r
 // Reconstruct-12 in FP64: unit = one link, rows 0-1 in FP64 (96 B), the full
 // FP64 product out (144 B).
 struct FormR12F64 {
-    static constexpr int kIn = 6, kOut = 9, kUnitsPerSite = 4, kWavesPerCU = SU3_WAVES_R12F64;
+    static constexpr int kIn = 6, kOut = 9, kUnitsPerSite = 4;
+    static constexpr WaveCaps kCaps = one_cap(SU3_WAVES_R12F64);
     typedef double B;
     typedef Link<double> Coef;
     __device__ static void load(const B *b, int pos, Coef &m) { load_link(b, pos, m); }
@@ -345,7 +352,8 @@ __device__ __forceinline__ void link_an(const S *x, const Link<S> &m, S *y)
 // a^H b, FP64: unit = one link (the whole link is needed for its columns),
 // 144 B in and out.
 struct FormAnF64 {
-    static constexpr int kIn = 9, kOut = 9, kUnitsPerSite = 4, kWavesPerCU = SU3_WAVES_AN;
+    static constexpr int kIn = 9, kOut = 9, kUnitsPerSite = 4;
+    static constexpr WaveCaps kCaps = kCapsAn;
     typedef double B;
     typedef Link<double> Coef;
     __device__ static void load(const B *b, int pos, Coef &m) { load_link(b, pos, m); }
@@ -360,7 +368,8 @@ struct FormAnF64 {
 
 // a^H b, FP32: unit = links 2w, 2w+1 (144 B in and out).
 struct FormAnF32 {
-    static constexpr int kIn = 9, kOut = 9, kUnitsPerSite = 2, kWavesPerCU = SU3_WAVES_AN;
+    static constexpr int kIn = 9, kOut = 9, kUnitsPerSite = 2;
+    static constexpr WaveCaps kCaps = kCapsAn;
     typedef float B;
     struct Coef {
         Link<float> m[2];
@@ -755,10 +764,10 @@ int soa_block_threads() { return kSoaBlock; }
 template <class F, bool kConjB = false>
 static hipError_t launch_aos(const void *a, const void *b, void *c, int64_t sites, hipStream_t s)
 {
-    static PadCache cache;
-    const int64_t grid = aos_grid<F>(sites);
-    const LaunchPlan plan = launch_plan(reinterpret_cast<const void *>(fwd_aos<F, kConjB, true>), F::kWavesPerCU,
-                                        kAosBlock, grid, cache);
+    static PadCache cache[3];
+    const int64_t grid = aos_grid<F>(sites), bytes = sites * (F::kUnitsPerSite * (F::kIn + F::kOut) * 16);
+    const LaunchPlan plan =
+        launch_plan(reinterpret_cast<const void *>(fwd_aos<F, kConjB, true>), F::kCaps, bytes, kAosBlock, grid, cache);
     return launch_k(plan.one_generation ? fwd_aos<F, kConjB, false> : fwd_aos<F, kConjB, true>, dim3((unsigned)grid),
                     dim3(kAosBlock), s, plan.pad, (const u4 *)a, (const typename F::B *)b, (u4 *)c,
                     sites * F::kUnitsPerSite);

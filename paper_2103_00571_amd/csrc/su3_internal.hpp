@@ -213,6 +213,25 @@ struct LaunchPlan {
     bool one_generation = false;
 };
 LaunchPlan launch_plan(const void *kernel, int waves, int block, int64_t grid, PadCache &cache);
+// Caps by the bytes a call moves: waves[0] up to upto[0], waves[1] up to
+// upto[1], waves[2] beyond, each with its own PadCache. A long stream runs best
+// with few wavefronts resident; a short one spends more of its time filling
+// and draining the CUs, where more of them help. The limits were placed by
+// runs over 1, 3 and 10 buffers in turn, so that no size loses with any.
+struct WaveCaps {
+    int64_t upto[2];
+    int waves[3];
+};
+constexpr WaveCaps one_cap(int waves)
+{
+    return {{INT64_MAX, INT64_MAX}, {waves, waves, waves}};
+}
+inline LaunchPlan launch_plan(const void *kernel, const WaveCaps &caps, int64_t bytes, int block, int64_t grid,
+                              PadCache (&cache)[3])
+{
+    const int k = bytes <= caps.upto[0] ? 0 : bytes <= caps.upto[1] ? 1 : 2;
+    return launch_plan(kernel, caps.waves[k], block, grid, cache[k]);
+}
 // The dynamic LDS of a cap of `waves` wavefronts per CU on device `dev`,
 // computed on every call (no cache).
 size_t occupancy_pad_for(const void *kernel, int waves, int block, int dev);

@@ -5,17 +5,19 @@
 
 #include <type_traits>
 
-// Resident wavefronts per CU for the reconstruct-12 unpack (9 KiB of stores
-// and 3 or 6 KiB of loads per wavefront).
-#ifndef SU3_WAVES_UNPACK_R12
-#define SU3_WAVES_UNPACK_R12 7
-#endif
-// ... and for the reconstruct-12 pack (9 KiB of loads per wavefront).
-#ifndef SU3_WAVES_PACK_R12
-#define SU3_WAVES_PACK_R12 6
-#endif
-
 namespace su3 {
+
+// Resident wavefronts per CU of the reconstruct-12 conversions, with FP32 and
+// FP64 rows. The unpack has 9 KiB of stores and 3 or 6 KiB of loads per
+// wavefront (FP64, 100,000 sites: 16.1 us with 7 and 16.7 with 6, 2,560,000: 391
+// and 385). The pack has 9 KiB of loads (FP32, 100,000 sites: 13.6 with 12 and
+// 14.5 with 6; 1,200,000: 143 with 6, 152 with 4, 148 with 12; 2,560,000: 303
+// with 6, 298 with 4; FP64, 200,000: 28.8 with 6, 29.8 with 4; 2,560,000: 377
+// and 367).
+constexpr WaveCaps kUnpackR12F32 = one_cap(7);
+constexpr WaveCaps kUnpackR12F64 = {{130000000, INT64_MAX}, {7, 6, 6}};
+constexpr WaveCaps kPackR12F32 = {{260000000, 1500000000}, {12, 6, 4}};
+constexpr WaveCaps kPackR12F64 = {{700000000, INT64_MAX}, {6, 4, 4}};
 
 // The FP32 pack and unpack and the general transposes loop over their items
 // with a grid stride, on a grid of up to kOnePass workgroups: one pass for
@@ -719,23 +721,25 @@ hipError_t launch_stream_shape(const void *a, const void *b, void *c, int64_t ti
 template <typename V>
 static hipError_t launch_pack_r12(const void *src, void *dst, int64_t links, hipStream_t s)
 {
-    static PadCache cache;
+    static PadCache cache[3];
     const int64_t grid = (links + 63) / 64;
     const LaunchPlan plan =
-        launch_plan(reinterpret_cast<const void *>(pack_r12<V, true>), SU3_WAVES_PACK_R12, 64, grid, cache);
-    return launch_k(plan.one_generation ? pack_r12<V, false> : pack_r12<V, true>, dim3((unsigned)grid), dim3(64), s, plan.pad,
-                    (const u4 *)src, (u4 *)dst, links);
+        launch_plan(reinterpret_cast<const void *>(pack_r12<V, true>), sizeof(V) == 8 ? kPackR12F32 : kPackR12F64,
+                    links * (144 + 6 * (int)sizeof(V)), 64, grid, cache);
+    return launch_k(plan.one_generation ? pack_r12<V, false> : pack_r12<V, true>, dim3((unsigned)grid), dim3(64), s,
+                    plan.pad, (const u4 *)src, (u4 *)dst, links);
 }
 
 template <typename V>
 static hipError_t launch_unpack_r12(const void *src, void *dst, int64_t links, hipStream_t s)
 {
-    static PadCache cache;
+    static PadCache cache[3];
     const int64_t grid = (links + 63) / 64;
     const LaunchPlan plan =
-        launch_plan(reinterpret_cast<const void *>(unpack_r12<V, true>), SU3_WAVES_UNPACK_R12, 64, grid, cache);
-    return launch_k(plan.one_generation ? unpack_r12<V, false> : unpack_r12<V, true>, dim3((unsigned)grid), dim3(64), s, plan.pad,
-                    (const u4 *)src, (u4 *)dst, links);
+        launch_plan(reinterpret_cast<const void *>(unpack_r12<V, true>), sizeof(V) == 8 ? kUnpackR12F32 : kUnpackR12F64,
+                    links * (144 + 6 * (int)sizeof(V)), 64, grid, cache);
+    return launch_k(plan.one_generation ? unpack_r12<V, false> : unpack_r12<V, true>, dim3((unsigned)grid), dim3(64), s,
+                    plan.pad, (const u4 *)src, (u4 *)dst, links);
 }
 
 // The BF16 conversions of `chunks` 16-byte chunks of the BF16 side (9 per

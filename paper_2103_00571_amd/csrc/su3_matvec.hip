@@ -16,13 +16,12 @@
 // lattice once.
 #include "su3_internal.hpp"
 
-// Resident wavefronts per CU: each carries 9.75 KiB of loads in flight; 9
-// measured best at L=48 in the XCD-contiguous tile order (6.61 TB/s FP64).
-#ifndef SU3_WAVES_MATVEC
-#define SU3_WAVES_MATVEC 9
-#endif
-
 namespace su3 {
+
+// Resident wavefronts per CU, each with 9.75 KiB of loads in flight; 16 fit.
+// 331,776 sites FP64: 44.3 us with 9, 42.0 with 16; 2,560,000: 323 with 7, 329
+// with 9, 343 with 16.
+constexpr WaveCaps kMvCaps = {{400000000, 1200000000}, {0, 9, 7}};
 
 constexpr int kMvBlock = 64;    // one wavefront per workgroup
 
@@ -115,9 +114,9 @@ int64_t mat_vec_grid(int precision, int64_t sites)
 template <typename S>
 static hipError_t launch_mv(const void *a, const void *v, void *w, int64_t sites, int64_t grid, hipStream_t s)
 {
-    static PadCache cache;
-    const LaunchPlan plan =
-        launch_plan(reinterpret_cast<const void *>(mat_vec<S, true>), SU3_WAVES_MATVEC, kMvBlock, grid, cache);
+    static PadCache cache[3];
+    const LaunchPlan plan = launch_plan(reinterpret_cast<const void *>(mat_vec<S, true>), kMvCaps,
+                                        sites * (102 * (int)sizeof(S)), kMvBlock, grid, cache);
     return launch_k(plan.one_generation ? mat_vec<S, false> : mat_vec<S, true>, dim3((unsigned)grid), dim3(kMvBlock), s,
                     plan.pad, (const u4 *)a, (const uint64_t *)v, (u4 *)w, sites);
 }

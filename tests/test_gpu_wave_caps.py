@@ -1,0 +1,61 @@
+"""Calls on either side of the traffic where a kernel changes its occupancy
+cap: a lattice taken in one call equals, bit for bit, the same lattice taken in
+pieces that stay below every such limit."""
+
+import pytest
+import torch
+
+from _gpu import dev, say
+
+pytestmark = pytest.mark.gpu
+
+# call, form, bytes per site read from a and written to c, limits in bytes
+CASES = [
+    ("nn", "SU3_R12_F32", 192, 288, [200000000]),
+    ("an", "SU3_F64", 576, 576, [600000000]),
+    ("an", "SU3_F32", 288, 288, [600000000]),
+    ("mat_vec", "SU3_F64", 576, 192, [400000000, 1200000000]),
+    ("mat_vec", "SU3_F32", 288, 96, [400000000, 1200000000]),
+    ("pack", "SU3_R12_F32", 576, 192, [260000000, 1500000000]),
+    ("pack", "SU3_R12_F64", 576, 384, [700000000]),
+    ("unpack", "SU3_R12_F64", 384, 576, [130000000]),
+]
+CASES = [(op, form, na, nc, limit, past) for op, form, na, nc, limits in CASES
+         for limit in limits for past in (0, 1)]
+
+
+@pytest.mark.parametrize("op,form,na,nc,limit,past", CASES)
+def test_either_side_of_a_cap(op, form, na, nc, limit, past):
+    from paper_2103_00571_amd import abi
+
+    nv = na // 12 if op == "mat_vec" else 0
+    sites = limit // (na + nc + nv) + past
+    say("%s %s sites=%d" % (op, form, sites))
+    f = getattr(abi, form)
+    real = torch.float64 if "F64" in form or op == "pack" else torch.float32
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(sites)
+    a = torch.randn(sites * na // real.itemsize, dtype=real, device=dev(), generator=gen).view(torch.uint8)
+    b = torch.randn(72, dtype=torch.float64 if "F64" in form else torch.float32, device=dev(), generator=gen)
+    v = torch.randn(max(sites * nv // real.itemsize, 1), dtype=real, device=dev(), generator=gen).view(torch.uint8)
+    stream = torch.cuda.current_stream().cuda_stream
+
+    def run(out, s0, n):
+        pa, pc, pv = a.data_ptr() + s0 * na, out.data_ptr() + s0 * nc, v.data_ptr() + s0 * nv
+        if op == "nn":
+            return abi.su3_mult_nn(pa, b.data_ptr(), pc, n, f, stream)
+        if op == "an":
+            return abi.su3_mult_an(pa, b.data_ptr(), pc, n, f, stream)
+        if op == "mat_vec":
+            return abi.su3_mat_vec(pa, pv, pc, n, f, stream)
+        return (abi.su3_pack if op == "pack" else abi.su3_unpack)(pa, pc, n, f, stream)
+
+    whole = torch.zeros(sites * nc, dtype=torch.uint8, device=dev())
+    parts = torch.zeros_like(whole)
+    assert run(whole, 0, sites) == 0
+    step = 100000
+    for s0 in range(0, sites, step):
+        assert run(parts, s0, min(step, sites - s0)) == 0
+    torch.cuda.synchronize()
+    assert torch.equal(whole, parts)
+    assert int(torch.count_nonzero(whole.view(torch.int64)[-nc // 8:])) > 0

@@ -516,22 +516,37 @@ __global__ __launch_bounds__(64) void unpack_r12(const u4 *__restrict__ src, u4 
 
 // ------------------------------------------------------------ stream copy
 // dst[i] = src[i] over 16-byte elements, one element per thread, with
-// nontemporal loads and stores; the grid covers the buffer once, so the
-// dispatcher streams it in address order. Workgroups of one wavefront.
+// nontemporal loads; the grid covers the buffer once, so the dispatcher streams
+// it in address order. Workgroups of one wavefront. Stores write through
+// (kThrough), or are nontemporal where the grid is at most 24 wavefronts per CU,
+// all resident at once.
+// Write-through against nontemporal, 576 B FP64 sites: 20,000 4.6 / 4.9 us,
+// 65,536 11.9 / 12.5, 663,552 112.6 / 114.5, 4,200,000 713 / 718 (6.79 TB/s). At
+// most 24 wavefronts per CU above 600 MB: 1% faster there, 2-6% slower below.
+// 2, 3 or 4 elements per thread, capped or not, and tiles in XCD order were 0
+// to 15% slower.
 constexpr int kCopyBlock = 64;
+constexpr int kCopyWaves = 24;
+constexpr int64_t kCopyCapBytes = 600000000;
 
+template <bool kThrough>
 __global__ __launch_bounds__(kCopyBlock) void stream_copy(const u4 *__restrict__ src, u4 *__restrict__ dst, int64_t n)
 {
-    const int64_t i = (int64_t)blockIdx.x * kCopyBlock + threadIdx.x;
-    if (i < n)
+    const int64_t base = (int64_t)blockIdx.x * kCopyBlock, i = base + threadIdx.x;
+    if constexpr (kThrough) {
+        const OutWindow out = out_window(dst + base, 16 * kCopyBlock);
+        if (i < n)
+            st_out<true>(out, 16 * threadIdx.x, ld_stream(src + i));
+    } else if (i < n) {
         st_stream(dst + i, ld_stream(src + i));
+    }
 }
 
 // Access-shape probe: wavefront w (the workgroup index, or with order 1 its
 // XCD-contiguous tile, xcd_order) reads chunks w*64*RA + 64 i + lane of a
 // (i < RA) and likewise of b, and writes chunks w*64*W + 64 i + lane of c,
 // the same whole-wavefront 1 KiB runs and per-lane chunk counts as the
-// kernels it stands beside, with no arithmetic beyond folding the loads
+// kernels it stands beside and their write-through stores, with no arithmetic beyond folding the loads
 // into the stored values (so that no load is dead).
 template <int RA, int RB, int W>
 __global__ __launch_bounds__(64) void stream_shape(const u4 *__restrict__ a, const u4 *__restrict__ b,
@@ -546,6 +561,7 @@ __global__ __launch_bounds__(64) void stream_shape(const u4 *__restrict__ a, con
 #pragma unroll
     for (int i = 0; i < RB; ++i)
         vb[i] = ld_stream(b + w * 64 * RB + 64 * i + lane);
+    const OutWindow out = out_window(c + w * 64 * W, 16 * 64 * W);
     u4 x = va[0];
 #pragma unroll
     for (int i = 1; i < RA; ++i)
@@ -557,7 +573,7 @@ __global__ __launch_bounds__(64) void stream_shape(const u4 *__restrict__ a, con
     for (int i = 0; i < W; ++i) {
         u4 o = x;
         o.x += (uint32_t)i;
-        st_stream(c + w * 64 * W + 64 * i + lane, o);
+        st_out<true>(out, 16 * (64 * i + lane), o);
     }
 }
 
@@ -679,8 +695,13 @@ hipError_t launch_aos_soa(const void *src, void *dst, int64_t sites, int64_t pit
 hipError_t launch_stream_copy(const void *src, void *dst, int64_t bytes, hipStream_t s)
 {
     const int64_t n = bytes / 16;
-    return launch_k(stream_copy, dim3((unsigned)((n + kCopyBlock - 1) / kCopyBlock)), dim3(kCopyBlock), s, 0,
-                    (const u4 *)src, (u4 *)dst, n);
+    const int64_t grid = (n + kCopyBlock - 1) / kCopyBlock;
+    static PadCache cache;
+    size_t pad = 0;
+    if (2 * bytes > kCopyCapBytes)
+        pad = launch_plan(reinterpret_cast<const void *>(stream_copy<true>), kCopyWaves, kCopyBlock, grid, cache).pad;
+    return launch_k(grid <= kCopyWaves * kCUs ? stream_copy<false> : stream_copy<true>, dim3((unsigned)grid),
+                    dim3(kCopyBlock), s, pad, (const u4 *)src, (u4 *)dst, n);
 }
 
 bool stream_shape_supported(int in_a, int in_b, int out)

@@ -59,3 +59,20 @@ def test_either_side_of_a_cap(op, form, na, nc, limit, past):
     torch.cuda.synchronize()
     assert torch.equal(whole, parts)
     assert int(torch.count_nonzero(whole.view(torch.int64)[-nc // 8:])) > 0
+
+
+# Where the plain copy changes its stores (6,144 KiB) and its cap (600 MB of
+# traffic), with a ragged last workgroup.
+@pytest.mark.parametrize("nbytes", [6144 * 1024 - 16, 6144 * 1024, 6144 * 1024 + 16, 300000000, 300000016])
+def test_copy_on_either_side(nbytes):
+    from paper_2103_00571_amd import ops
+
+    say("copy of %d bytes" % nbytes)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(nbytes)
+    src = torch.randint(0, 256, (nbytes,), dtype=torch.uint8, device=dev(), generator=gen)
+    whole = torch.full((nbytes + 4096,), 7, dtype=torch.uint8, device=dev())
+    ops.stream_copy(src, whole[2048:2048 + nbytes])
+    torch.cuda.synchronize()
+    assert torch.equal(whole[2048:2048 + nbytes], src)
+    assert bool((whole[:2048] == 7).all()) and bool((whole[2048 + nbytes:] == 7).all())

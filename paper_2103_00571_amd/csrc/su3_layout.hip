@@ -128,12 +128,12 @@ __global__ __launch_bounds__(kBlock) void transpose_aos_soa(const V *__restrict_
 // matter. So the tile and the number of resident workgroups set the bytes in
 // flight, and many threads with few elements each keep a tile's life short.
 // launch_aos_soa states which tile serves which size.
-// kThrough: write-through stores (OutWindow) instead of nontemporal ones; from
-// planes also the grouped tile order (group_order), which alone is worth 1-2%
-// and with these stores 4-5% (groups of 2 to 64 and all the tiles of an XCD
-// together were tried). To planes the groups collide where the plane stride is
-// a power of two (2^17 and 2^19 sites: 0.84 to 0.93 of the speed) and gain 1%
-// elsewhere, so workgroups take their tiles in order.
+// kThrough: write-through stores (OutWindow) instead of nontemporal ones.
+// kGroup: the grouped tile order (group_order), which alone is worth 1-2% and
+// with these stores 4-5% (groups of 2, 4, 16, 32 and 64 and all the tiles of an
+// XCD together were 0 to 4% slower). To planes the groups collide where the
+// plane stride is near a power of two (0.84 to 0.98 of the speed from 2^17 to
+// 2^21 sites) and gain nothing up to a million sites; they gain 1-6% beyond.
 //
 // kHalo, for planes that do not start on 128-byte lines (a site count that
 // is no multiple of 8 in FP64 or 16 in FP32, dense): a run cut at the tile's
@@ -144,7 +144,7 @@ __global__ __launch_bounds__(kBlock) void transpose_aos_soa(const V *__restrict_
 // one line's worth of sites past its tile and moves each plane's window up to
 // that plane's next line boundary, so that every line is written whole by one
 // workgroup; the first tile also writes the sites before its window.
-template <typename V, int TS, int B, bool kHalo, bool kThrough>
+template <typename V, int TS, int B, bool kHalo, bool kThrough, bool kGroup>
 __global__ __launch_bounds__(B) void to_soa_tile(const V *__restrict__ src, V *__restrict__ dst, int64_t n,
                                                  int64_t pitch)
 {
@@ -153,7 +153,8 @@ __global__ __launch_bounds__(B) void to_soa_tile(const V *__restrict__ src, V *_
     constexpr int kIn = (36 * W + B - 1) / B, kOut = 36 * TS / B;
     static_assert(kOut * B == 36 * TS && TS % H == 0, "a tile splits evenly over the workgroup and into lines");
     __shared__ V tile[36][W + 1];
-    const int64_t s0 = (int64_t)blockIdx.x * TS, nin = n * 36;
+    const int64_t t = kGroup ? group_order(blockIdx.x, gridDim.x) : (int64_t)blockIdx.x;
+    const int64_t s0 = t * TS, nin = n * 36;
     V v[kIn];
 #pragma unroll
     for (int i = 0; i < kIn; ++i) {
@@ -191,7 +192,7 @@ __global__ __launch_bounds__(B) void to_soa_tile(const V *__restrict__ src, V *_
             st_stream(dst + (int64_t)p * pitch + s, o[i]);
         }
     }
-    if (kHalo && blockIdx.x == 0) {
+    if (kHalo && t == 0) {
         for (int e = threadIdx.x; e < 36 * H; e += B) {
             const int p = e / H, s = e % H;
             if (s < shift(p) && s < n)
@@ -202,6 +203,7 @@ __global__ __launch_bounds__(B) void to_soa_tile(const V *__restrict__ src, V *_
 
 // kNt: nontemporal plane loads. Where planes do not start on lines, two
 // workgroups read the line at a tile's edge, and FP32 keeps it in the cache.
+// Write-through stores go with the grouped order here.
 template <typename V, int TS, int B, bool kNt, bool kThrough>
 __global__ __launch_bounds__(B) void to_aos_tile(const V *__restrict__ src, V *__restrict__ dst, int64_t n,
                                                  int64_t pitch)
@@ -598,10 +600,11 @@ static hipError_t launch_tiles(const VS *src, VD *dst, int64_t n, int64_t pitch,
     const LaunchPlan plan = launch_plan(reinterpret_cast<const void *>(K), kPerCU * (B / 64), B, grid, cache);
     return launch_k(K, dim3((unsigned)grid), dim3(B), s, plan.pad, src, dst, n, pitch);
 }
-template <typename V, int TS, int B, bool kHalo, bool kThrough, int kPerCU>
+template <typename V, int TS, int B, bool kHalo, bool kThrough, bool kGroup, int kPerCU>
 static hipError_t launch_to_soa(const void *src, void *dst, int64_t n, int64_t pitch, hipStream_t s)
 {
-    return launch_tiles<to_soa_tile<V, TS, B, kHalo, kThrough>, TS, B, kPerCU>((const V *)src, (V *)dst, n, pitch, s);
+    return launch_tiles<to_soa_tile<V, TS, B, kHalo, kThrough, kGroup>, TS, B, kPerCU>((const V *)src, (V *)dst, n,
+                                                                                      pitch, s);
 }
 template <typename V, int TS, int B, bool kNt, bool kThrough, int kPerCU>
 static hipError_t launch_to_aos(const void *src, void *dst, int64_t n, int64_t pitch, hipStream_t s)
@@ -628,8 +631,11 @@ static hipError_t launch_general(const void *src, void *dst, int64_t n, int64_t 
 //    262,144 sites 384 threads, three per CU, write-through (81,920: 17.0,
 //    160,000: 30.4, 230,400: 46.8; 1.00 to 1.17 times the next form at 8
 //    sizes, dense and padded), beyond that 576 threads, nontemporal (24^4: 64 /
-//    78, 40^4: 480 / 565, 48^4: 1054 / 1150; the form before it is level
-//    there and 5% slower at 2^20). Off lines, 128-site tiles with the
+//    78; the form before it is level there and 5% slower at 2^20), and above
+//    1,100,000 sites grouped and write-through (40^4: 490 / 565, 48^4: 1018 /
+//    1150; 0.98 at 2^21 padded and 1.01 to 1.06 at 14 other sizes and pitches
+//    against nontemporal in order, 0.91 to 1.0 at 262,656 to 663,552
+//    sites). Off lines, 128-site tiles with the
 //    halo, two per CU up to 131,072 sites (65,537: 13.5 / 15.9) and one
 //    above (31^4: 193 / 250, 2,560,001: 533 / 630).
 //  FP64 from planes, on lines: up to 65,536 sites as above; beyond, 32-site
@@ -668,12 +674,13 @@ hipError_t launch_aos_soa(const void *src, void *dst, int64_t sites, int64_t pit
         if (n <= 49152 || huge || (!to_soa && !lines && n <= 196608))
             return launch_general<d2, true>(src, dst, n, pitch, to_soa, s);
         if (to_soa && !lines)
-            return n <= 131072 ? launch_to_soa<d2, 128, 768, true, false, 0>(src, dst, n, pitch, s)
-                               : launch_to_soa<d2, 128, 768, true, false, 1>(src, dst, n, pitch, s);
+            return n <= 131072 ? launch_to_soa<d2, 128, 768, true, false, false, 0>(src, dst, n, pitch, s)
+                               : launch_to_soa<d2, 128, 768, true, false, false, 1>(src, dst, n, pitch, s);
         if (to_soa)
-            return n <= 65536              ? launch_to_soa<d2, 128, 768, false, false, 0>(src, dst, n, pitch, s)
-                   : n <= 262144 && window ? launch_to_soa<d2, 32, 384, false, true, 3>(src, dst, n, pitch, s)
-                                           : launch_to_soa<d2, 32, 576, false, false, 0>(src, dst, n, pitch, s);
+            return n <= 65536               ? launch_to_soa<d2, 128, 768, false, false, false, 0>(src, dst, n, pitch, s)
+                   : n <= 262144 && window  ? launch_to_soa<d2, 32, 384, false, true, false, 3>(src, dst, n, pitch, s)
+                   : n <= 1100000 || !window ? launch_to_soa<d2, 32, 576, false, false, false, 0>(src, dst, n, pitch, s)
+                                            : launch_to_soa<d2, 32, 576, false, true, true, 3>(src, dst, n, pitch, s);
         return n <= 65536 ? launch_to_aos<d2, 128, 768, true, false, 0>(src, dst, n, pitch, s)
                : lines    ? launch_to_aos<d2, 32, 384, true, true, 3>(src, dst, n, pitch, s)
                           : launch_to_aos<d2, 128, 768, true, true, 1>(src, dst, n, pitch, s);
@@ -681,14 +688,14 @@ hipError_t launch_aos_soa(const void *src, void *dst, int64_t sites, int64_t pit
     if (huge || (!lines && n <= 49152))
         return launch_general<f2, false>(src, dst, n, pitch, to_soa, s);
     if (!lines)
-        return to_soa ? launch_to_soa<f2, 128, 256, true, false, 2>(src, dst, n, pitch, s)
+        return to_soa ? launch_to_soa<f2, 128, 256, true, false, false, 2>(src, dst, n, pitch, s)
                       : launch_to_aos<f2, 128, 256, false, false, 0>(src, dst, n, pitch, s);
     if (n <= 131072)
         return to_soa ? launch_tiles<to_soa_pairs<64, 128>, 64, 128, 0>((const f4 *)src, (f2 *)dst, n, pitch, s)
                       : launch_tiles<to_aos_pairs<64, 128>, 64, 128, 0>((const f2 *)src, (f4 *)dst, n, pitch, s);
     if (!to_soa)
         return launch_to_aos<f2, 64, 768, true, true, 0>(src, dst, n, pitch, s);
-    return n <= 400000 && window ? launch_to_soa<f2, 64, 256, false, true, 3>(src, dst, n, pitch, s)
+    return n <= 400000 && window ? launch_to_soa<f2, 64, 256, false, true, false, 3>(src, dst, n, pitch, s)
                                  : launch_tiles<to_soa_pairs<64, 576>, 64, 576, 0>((const f4 *)src, (f2 *)dst, n, pitch, s);
 }
 

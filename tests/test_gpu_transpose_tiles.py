@@ -53,7 +53,8 @@ def test_transforms_at_the_edges(sites, dtype, offset):
 # Both sides of the sizes where the write-through forms begin and end, and a
 # tail of tiles shorter than one group of the tile order.
 @pytest.mark.parametrize("dtype", [torch.complex128, torch.complex64])
-@pytest.mark.parametrize("sites", [65552, 131104, 200000, 262144, 262160, 400000, 400016, 525328])
+@pytest.mark.parametrize("sites", [65552, 131104, 200000, 262144, 262160, 400000, 400016, 525328,
+                                   1100000, 1100032])
 def test_grouped_and_write_through_tiles(sites, dtype):
     test_transforms_at_the_edges(sites, dtype, 0)
 
@@ -65,6 +66,8 @@ def test_long_plane_strides(pitch, dtype):
     from paper_2103_00571_amd import abi
 
     form, sites = (abi.SU3_F64 if dtype == torch.complex128 else abi.SU3_F32), 140000
+    if pitch > 15 << 20:
+        sites = 1100048     # the form for larger lattices
     say("transpose sites=%d pitch=%d %s" % (sites, pitch, dtype))
     x = torch.randn((sites, 36), dtype=dtype, device=dev())
     planes = torch.zeros((36, pitch), dtype=dtype, device=dev())

@@ -53,11 +53,13 @@ constexpr int kBwdThreads = 64 * kBwdWaves;
 // stream one contiguous front instead of each its own run.
 // kEarly: a wavefront's first loads are issued before the barrier that
 // publishes b, so they do not wait for it.
-template <typename S_, int kSub_, int kSteps_, int kBatch_, bool kEarly_, int kWaves_>
+// kGroup: the workgroups take the groups in the grouped order, 16 consecutive
+// per XCD (each group's work and partial slot stay, so dB does too).
+template <typename S_, int kSub_, int kSteps_, int kBatch_, bool kEarly_, int kWaves_, bool kGroup_ = false>
 struct BwdForm {
     typedef S_ S;
     static constexpr int kSub = kSub_, kSteps = kSteps_, kBatch = kBatch_, kWaves = kWaves_;
-    static constexpr bool kEarly = kEarly_;
+    static constexpr bool kEarly = kEarly_, kGroup = kGroup_;
     static constexpr int kTiles = kBwdWaves * kSub * kSteps;   // 64-row tiles per workgroup
 };
 // Which form takes which lattice, by the last site count of each (sweeps of 1,
@@ -67,16 +69,23 @@ struct BwdForm {
 // The lines at 16,384 to 131,072 sites lie where the whole grid is resident
 // at once with 1, 2 or 4 steps.
 //  FP64: 4,096 sites 6.2 / 8.4, 16,384 9.6 / 10.2, 20,000 10.8 / 12.0, 131,072
-//  42.6 / 43.2, 160,000 50.4 / 52.1, 331,776 97 / 98, 2^20 288 / 291, 2,000,000
-//  546 / 556 (2 steps there: 567).
+//  42.6 / 43.2, 160,000 49.9 / 52.1, 331,776 96 / 98, 2^20 288 / 292, 2,000,000
+//  542 / 556 (2 steps there: 567).
 //  FP32: 4,096 sites 6.6 / 7.5, 32,768 9.9 / 10.7, 100,000 20.7 / 21.2, 331,776
 //  52.3 / 52.9; above 700,000 sites kEarly loses 1-5% and a batch 1-2%.
-typedef BwdForm<double, 1, 1, 0, true, 12> BwdF64x1;     // to 16,384 sites
-typedef BwdForm<double, 1, 2, 256, true, 12> BwdF64x2;   // to 32,768 and from 131,072 to 400,000
-typedef BwdForm<double, 1, 4, 256, true, 9> BwdF64x4;    // to 131,072 and from 400,000
-typedef BwdForm<float, 2, 1, 0, true, 12> BwdF32x1;      // to 32,768
-typedef BwdForm<float, 2, 2, 256, true, 12> BwdF32x2;    // to 700,000
-typedef BwdForm<float, 2, 2, 0, false, 12> BwdF32Large;  // above
+// kGroup is worth 1-2% in FP64 from 131,072 sites (331,776: 97.2 -> 96.0,
+// 2,560,000: 711 -> 702) and 0-1.5% in FP32 from 700,000; below, it loses up to
+// 5%, as does a run-time choice of the order. Groups of 2 to 64, and batches of
+// 128 and 512 with them, were level or slower, and one contiguous eighth of
+// the groups per XCD 4-8% slower.
+typedef BwdForm<double, 1, 1, 0, true, 12> BwdF64x1;            // to 16,384 sites
+typedef BwdForm<double, 1, 2, 256, true, 12> BwdF64x2;          // to 32,768
+typedef BwdForm<double, 1, 4, 256, true, 9> BwdF64x4;           // to 131,072
+typedef BwdForm<double, 1, 2, 256, true, 12, true> BwdF64x2g;   // to 400,000
+typedef BwdForm<double, 1, 4, 256, true, 9, true> BwdF64x4g;    // above
+typedef BwdForm<float, 2, 1, 0, true, 12> BwdF32x1;             // to 32,768
+typedef BwdForm<float, 2, 2, 256, true, 12> BwdF32x2;           // to 700,000
+typedef BwdForm<float, 2, 2, 0, false, 12, true> BwdF32x2g;     // above
 // dB alone (kSteps 0: the step count is a launch argument, db_steps).
 typedef BwdForm<double, 1, 0, 256, true, 9> DbF64;
 typedef BwdForm<float, 2, 0, 256, true, 9> DbF32;
@@ -157,7 +166,7 @@ __global__ __launch_bounds__(kBwdThreads) void bwd_tiles(const u4 *__restrict__ 
     u4 *stg = reinterpret_cast<u4 *>(tilebuf[wv]);    // dC at [0, 192), A at [192, 384)
     double *red = reinterpret_cast<double *>(tilebuf[wv]);
     // this workgroup's tile group; its partial goes to slot grp
-    const int64_t grp = blockIdx.x;
+    const int64_t grp = F::kGroup ? group_order<16>(blockIdx.x, gridDim.x) : (int64_t)blockIdx.x;
     // the wavefront's first 64-row tile t0; it takes t0 + D i for
     // i < kSub * nsteps (D a multiple of 3)
     const int64_t per = (int64_t)kBwdWaves * kSub * nsteps;   // tiles of a workgroup
@@ -433,11 +442,12 @@ __global__ __launch_bounds__(128) void bwd_zero(T *__restrict__ db)
 static int64_t tiles_per_group(int64_t n, int precision)
 {
     if (precision == 0)
-        return n <= kLast64[0]                       ? BwdF64x1::kTiles
-               : n <= kLast64[1]                     ? BwdF64x2::kTiles
-               : n <= kLast64[2] || n > kLast64[3] ? BwdF64x4::kTiles
-                                                     : BwdF64x2::kTiles;
-    return n <= kLast32[0] ? BwdF32x1::kTiles : BwdF32x2::kTiles;   // and BwdF32Large
+        return n <= kLast64[0]   ? BwdF64x1::kTiles
+               : n <= kLast64[1] ? BwdF64x2::kTiles
+               : n <= kLast64[2] ? BwdF64x4::kTiles
+               : n <= kLast64[3] ? BwdF64x2g::kTiles
+                                 : BwdF64x4g::kTiles;
+    return n <= kLast32[0] ? BwdF32x1::kTiles : n <= kLast32[1] ? BwdF32x2::kTiles : BwdF32x2g::kTiles;
 }
 
 // Workgroups of stage 1 for `sites` (a function of the size and form only).
@@ -509,18 +519,17 @@ static hipError_t launch_sum(double *ws, uint32_t *counts, int64_t groups, void 
 hipError_t launch_bwd(const void *a, const void *b, const void *dc, void *da, void *db, bool db_float, int64_t sites,
                       int precision, double *ws, hipStream_t s)
 {
-    const int64_t groups = bwd_groups(sites, precision), per = tiles_per_group(sites, precision);
+    const int64_t groups = bwd_groups(sites, precision);
     uint32_t *counts = reinterpret_cast<uint32_t *>(ws + 72 * groups);
-    hipError_t e;
-    if (precision == 0)
-        e = (per == BwdF64x1::kTiles   ? launch_tiles_f<BwdF64x1, true>
-             : per == BwdF64x2::kTiles ? launch_tiles_f<BwdF64x2, true>
-                                       : launch_tiles_f<BwdF64x4, true>)(a, b, dc, da, sites, ws, counts, groups, 0, s);
-    else
-        e = (per == BwdF32x1::kTiles    ? launch_tiles_f<BwdF32x1, true>
-             : sites <= kLast32[1] ? launch_tiles_f<BwdF32x2, true>
-                                        : launch_tiles_f<BwdF32Large, true>)(a, b, dc, da, sites, ws, counts, groups, 0,
-                                                                             s);
+    auto *launch = precision != 0 ? (sites <= kLast32[0]   ? launch_tiles_f<BwdF32x1, true>
+                                     : sites <= kLast32[1] ? launch_tiles_f<BwdF32x2, true>
+                                                           : launch_tiles_f<BwdF32x2g, true>)
+                   : sites <= kLast64[0] ? launch_tiles_f<BwdF64x1, true>
+                   : sites <= kLast64[1] ? launch_tiles_f<BwdF64x2, true>
+                   : sites <= kLast64[2] ? launch_tiles_f<BwdF64x4, true>
+                   : sites <= kLast64[3] ? launch_tiles_f<BwdF64x2g, true>
+                                         : launch_tiles_f<BwdF64x4g, true>;
+    const hipError_t e = launch(a, b, dc, da, sites, ws, counts, groups, 0, s);
     return e != hipSuccess ? e : launch_sum(ws, counts, groups, db, db_float, s);
 }
 

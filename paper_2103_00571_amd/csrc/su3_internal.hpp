@@ -77,13 +77,14 @@ __device__ __forceinline__ int64_t xcd_order(int64_t bid, int64_t nb)
     return x * q + (x < r ? x : r) + bid / kXcds;
 }
 
-// Grouped tile order: within every 64 tiles each XCD takes 8 consecutive ones,
-// so that its runs on a plane join up while the whole grid still walks the
-// array in order. A bijection on [0, nb): the tail of less than 64 keeps the
-// index.
+// Grouped tile order: within every 8 * kGroup tiles each XCD takes kGroup
+// consecutive ones, so that its runs join up while the whole grid still walks
+// the array in order. A bijection on [0, nb): the tail of less than 8 * kGroup
+// keeps the index.
+template <int kGroup = 8>
 __device__ __forceinline__ int64_t group_order(int64_t bid, int64_t nb)
 {
-    constexpr int kGroup = 8, kSpan = kXcds * kGroup;
+    constexpr int kSpan = kXcds * kGroup;
     const int64_t k = bid / kSpan;
     const int r = (int)(bid - k * kSpan);
     return (k + 1) * kSpan > nb ? bid : k * kSpan + r % kXcds * kGroup + r / kXcds;

@@ -768,8 +768,8 @@ static hipError_t launch_aos(const void *a, const void *b, void *c, int64_t site
     const int64_t grid = aos_grid<F>(sites), bytes = sites * (F::kUnitsPerSite * (F::kIn + F::kOut) * 16);
     const LaunchPlan plan =
         launch_plan(reinterpret_cast<const void *>(fwd_aos<F, kConjB, true>), F::kCaps, bytes, kAosBlock, grid, cache);
-    return launch_k(plan.one_generation ? fwd_aos<F, kConjB, false> : fwd_aos<F, kConjB, true>, dim3((unsigned)grid),
-                    dim3(kAosBlock), s, plan.pad, (const u4 *)a, (const typename F::B *)b, (u4 *)c,
+    return launch_k(write_through(plan, bytes, 300000000) ? fwd_aos<F, kConjB, true> : fwd_aos<F, kConjB, false>,
+                    dim3((unsigned)grid), dim3(kAosBlock), s, plan.pad, (const u4 *)a, (const typename F::B *)b, (u4 *)c,
                     sites * F::kUnitsPerSite);
 }
 

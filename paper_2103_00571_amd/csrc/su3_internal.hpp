@@ -233,6 +233,21 @@ inline LaunchPlan launch_plan(const void *kernel, const WaveCaps &caps, int64_t 
     const int k = bytes <= caps.upto[0] ? 0 : bytes <= caps.upto[1] ? 1 : 2;
     return launch_plan(kernel, caps.waves[k], block, grid, cache[k]);
 }
+// Where the stores of a grid of more than one generation write through. Up to a
+// few hundred megabytes of traffic they win 6-16% (the output then shares the
+// 256 MiB Infinity Cache with inputs that a caller comes back to), and above
+// 600 MB 0.5-2%. In between they depend on where the buffers lie: FP32 a b^H at
+// 322 and 354 MB 52.0 and 58.4 us against 50.6 and 56.2 with nontemporal
+// stores into two outputs in turn, level into one; FP32 matrix-vector at 428
+// MB 65.1 to 75.7 against 69.0. There the stores stay nontemporal. `from` is
+// where a kernel's gain ends: 300 MB for one byte written per byte read, 400
+// MB for less; `again` is where it returns (matrix-vector: 1.2 GB; at 612 MB
+// 101 us against 97).
+constexpr int64_t kThroughAgain = 600000000;
+inline bool write_through(const LaunchPlan &plan, int64_t bytes, int64_t from, int64_t again = kThroughAgain)
+{
+    return !plan.one_generation && (bytes <= from || bytes > again);
+}
 // The dynamic LDS of a cap of `waves` wavefronts per CU on device `dev`,
 // computed on every call (no cache).
 size_t occupancy_pad_for(const void *kernel, int waves, int block, int dev);

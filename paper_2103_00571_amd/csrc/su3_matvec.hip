@@ -115,10 +115,11 @@ template <typename S>
 static hipError_t launch_mv(const void *a, const void *v, void *w, int64_t sites, int64_t grid, hipStream_t s)
 {
     static PadCache cache[3];
-    const LaunchPlan plan = launch_plan(reinterpret_cast<const void *>(mat_vec<S, true>), kMvCaps,
-                                        sites * (102 * (int)sizeof(S)), kMvBlock, grid, cache);
-    return launch_k(plan.one_generation ? mat_vec<S, false> : mat_vec<S, true>, dim3((unsigned)grid), dim3(kMvBlock), s,
-                    plan.pad, (const u4 *)a, (const uint64_t *)v, (u4 *)w, sites);
+    const int64_t bytes = sites * (102 * (int)sizeof(S));
+    const LaunchPlan plan =
+        launch_plan(reinterpret_cast<const void *>(mat_vec<S, true>), kMvCaps, bytes, kMvBlock, grid, cache);
+    return launch_k(write_through(plan, bytes, kMvCaps.upto[0], kMvCaps.upto[1]) ? mat_vec<S, true> : mat_vec<S, false>,
+                    dim3((unsigned)grid), dim3(kMvBlock), s, plan.pad, (const u4 *)a, (const uint64_t *)v, (u4 *)w, sites);
 }
 
 hipError_t launch_mat_vec(const void *a, const void *v, void *w, int64_t sites, int precision, hipStream_t s)

@@ -9,15 +9,18 @@ from _gpu import dev, say
 
 pytestmark = pytest.mark.gpu
 
+# (and of the traffic where the stores change their cache policy)
 # call, form, bytes per site read from a and written to c, limits in bytes
 CASES = [
+    ("nn", "SU3_F64", 576, 576, [300000000, 600000000]),
+    ("nn", "SU3_BF16", 144, 144, [300000000, 600000000]),
     ("nn", "SU3_R12_F32", 192, 288, [200000000]),
     ("an", "SU3_F64", 576, 576, [600000000]),
     ("an", "SU3_F32", 288, 288, [600000000]),
     ("mat_vec", "SU3_F64", 576, 192, [400000000, 1200000000]),
     ("mat_vec", "SU3_F32", 288, 96, [400000000, 1200000000]),
     ("pack", "SU3_R12_F32", 576, 192, [260000000, 1500000000]),
-    ("pack", "SU3_R12_F64", 576, 384, [700000000]),
+    ("pack", "SU3_R12_F64", 576, 384, [400000000, 600000000, 700000000]),
     ("unpack", "SU3_R12_F64", 384, 576, [130000000]),
 ]
 CASES = [(op, form, na, nc, limit, past) for op, form, na, nc, limits in CASES
@@ -35,6 +38,8 @@ def test_either_side_of_a_cap(op, form, na, nc, limit, past):
     real = torch.float64 if "F64" in form or op == "pack" else torch.float32
     gen = torch.Generator(device="cuda")
     gen.manual_seed(sites)
+    if form == "SU3_BF16":
+        real = torch.bfloat16
     a = torch.randn(sites * na // real.itemsize, dtype=real, device=dev(), generator=gen).view(torch.uint8)
     b = torch.randn(72, dtype=torch.float64 if "F64" in form else torch.float32, device=dev(), generator=gen)
     v = torch.randn(max(sites * nv // real.itemsize, 1), dtype=real, device=dev(), generator=gen).view(torch.uint8)

@@ -166,10 +166,10 @@ int su3_mult_nn_soa(const void *a, const void *b, void *c, int64_t sites,
  * not a multiple of 8 (SU3_F64) or 16 (SU3_F32), dense planes also start off
  * 128-byte boundaries; the product and the AoS -> SoA transform then shift
  * their runs to whole lines and run 3-15% below their rate on aligned planes.
- * A pitch that is a multiple of 64 sites keeps every plane aligned. su3_soa_pitch gives the pitch at which the product
- * streams at the site-major rate. Arguments,
- * alignment and errors as su3_mult_nn_soa; a and c each span 36*pitch
- * complex elements, c must not overlap a or b; pitch < sites returns
+ * A pitch that is a multiple of 64 sites keeps every plane aligned.
+ * su3_soa_pitch gives the pitch at which the product streams at the site-major
+ * rate. Arguments, alignment and errors as su3_mult_nn_soa; a and c each span
+ * 36*pitch complex elements, c must not overlap a or b; pitch < sites returns
  * SU3_ERR_SIZE.
  */
 int su3_mult_nn_soa_pitched(const void *a, const void *b, void *c, int64_t sites,

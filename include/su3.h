@@ -280,10 +280,9 @@ int su3_mult_nn_grad(const void *a, const void *b, const void *dc, void *da, voi
  * su3_mult_nn_bwd without ws and ws_bytes, except that SU3_ERR_WORKSPACE
  * means the lattice needs more workspace than the array holds:
  * su3_mult_nn_bwd_workspace_bytes(sites, precision) > SU3_BWD_SCRATCH_BYTES,
- * i.e. above about 7.4 million sites in FP64 and 14.9 million in FP32 (an
- * L = 48 lattice, 5,308,416 sites, fits in both). The array's device address
- * is looked up on the first call on each device, so make that first call
- * outside graph capture. Every call on a device shares that device's array:
+ * i.e. above about 7.4 million sites (an L = 48 lattice, 5,308,416 sites,
+ * fits). The array's device address is looked up on the first call on each
+ * device, so make that first call outside graph capture. Every call on a device shares that device's array:
  * calls that can overlap in time on one device (two streams, two host
  * threads, two graphs) race on it and must be ordered by the caller.
  */

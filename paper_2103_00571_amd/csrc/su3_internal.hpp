@@ -233,20 +233,21 @@ inline LaunchPlan launch_plan(const void *kernel, const WaveCaps &caps, int64_t 
     const int k = bytes <= caps.upto[0] ? 0 : bytes <= caps.upto[1] ? 1 : 2;
     return launch_plan(kernel, caps.waves[k], block, grid, cache[k]);
 }
-// Where the stores of a grid of more than one generation write through. Up to a
-// few hundred megabytes of traffic they win 6-16% (the output then shares the
-// 256 MiB Infinity Cache with inputs that a caller comes back to), and above
-// 600 MB 0.5-2%. In between they depend on where the buffers lie: FP32 a b^H at
-// 322 and 354 MB 52.0 and 58.4 us against 50.6 and 56.2 with nontemporal
-// stores into two outputs in turn, level into one; FP32 matrix-vector at 428
-// MB 65.1 to 75.7 against 69.0. There the stores stay nontemporal. `from` is
-// where a kernel's gain ends: 300 MB for one byte written per byte read, 400
-// MB for less; `again` is where it returns (matrix-vector: 1.2 GB; at 612 MB
-// 101 us against 97).
-constexpr int64_t kThroughAgain = 600000000;
-inline bool write_through(const LaunchPlan &plan, int64_t bytes, int64_t from, int64_t again = kThroughAgain)
+// Where the stores of a grid of more than one generation write through: while
+// the outputs that a caller has in turn fit the 256 MiB Infinity Cache together
+// (`written` up to `fit`: three outputs of a product, two of a conversion,
+// which always writes a new one) they win 6-16%, and above `again` bytes of
+// traffic 0.5-2%. In between they depend on how many buffers are in turn and
+// where those lie, and the stores stay nontemporal. FP64 a b on three inputs,
+// into one new output each time and into three: 160,000 sites 26.5 and 26.8 us
+// against 29.6 and 29.4, 190,000 30.8 and 36.0 against 34.6 and 34.8; FP32 at
+// 614,656 sites 58.4 and 56.0 against 56.2. FP32 matrix-vector at 428 MB 65.1
+// and 75.7 against 69.0, at 612 MB 101 against 97.
+constexpr int64_t kFitProduct = 96000000, kFitConversion = 144000000, kThroughAgain = 600000000;
+inline bool write_through(const LaunchPlan &plan, int64_t written, int64_t fit, int64_t bytes,
+                          int64_t again = kThroughAgain)
 {
-    return !plan.one_generation && (bytes <= from || bytes > again);
+    return !plan.one_generation && (written <= fit || bytes > again);
 }
 // The dynamic LDS of a cap of `waves` wavefronts per CU on device `dev`,
 // computed on every call (no cache).

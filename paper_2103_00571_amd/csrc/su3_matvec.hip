@@ -130,8 +130,9 @@ static hipError_t launch_mv(const void *a, const void *v, void *w, int64_t sites
     const int64_t bytes = sites * (102 * (int)sizeof(S));
     const LaunchPlan plan =
         launch_plan(reinterpret_cast<const void *>(mat_vec<S, true>), kMvCaps, bytes, kMvBlock, grid, cache);
-    return launch_k(write_through(plan, bytes, kMvCaps.upto[0], kMvCaps.upto[1]) ? mat_vec<S, true> : mat_vec<S, false>,
-                    dim3((unsigned)grid), dim3(kMvBlock), s, plan.pad, (const u4 *)a, (const uint64_t *)v, (u4 *)w, sites);
+    const bool through = write_through(plan, sites * (24 * (int)sizeof(S)), kFitProduct, bytes, kMvCaps.upto[1]);
+    return launch_k(through ? mat_vec<S, true> : mat_vec<S, false>, dim3((unsigned)grid), dim3(kMvBlock), s, plan.pad,
+                    (const u4 *)a, (const uint64_t *)v, (u4 *)w, sites);
 }
 
 hipError_t launch_mat_vec(const void *a, const void *v, void *w, int64_t sites, int precision, hipStream_t s)

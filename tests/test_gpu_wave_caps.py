@@ -12,15 +12,15 @@ pytestmark = pytest.mark.gpu
 # (and of the traffic where the stores change their cache policy)
 # call, form, bytes per site read from a and written to c, limits in bytes
 CASES = [
-    ("nn", "SU3_F64", 576, 576, [300000000, 600000000]),
-    ("nn", "SU3_BF16", 144, 144, [300000000, 600000000]),
-    ("nn", "SU3_R12_F32", 192, 288, [200000000]),
+    ("nn", "SU3_F64", 576, 576, [192000000, 600000000]),
+    ("nn", "SU3_BF16", 144, 144, [192000000, 600000000]),
+    ("nn", "SU3_R12_F32", 192, 288, [160000000, 200000000, 600000000]),
     ("an", "SU3_F64", 576, 576, [600000000]),
     ("an", "SU3_F32", 288, 288, [600000000]),
-    ("mat_vec", "SU3_F64", 576, 192, [400000000, 1200000000]),
+    ("mat_vec", "SU3_F64", 576, 192, [400000000, 408000000, 1200000000]),
     ("mat_vec", "SU3_F32", 288, 96, [400000000, 1200000000]),
     ("pack", "SU3_R12_F32", 576, 192, [260000000, 1500000000]),
-    ("pack", "SU3_R12_F64", 576, 384, [400000000, 600000000, 700000000]),
+    ("pack", "SU3_R12_F64", 576, 384, [360000000, 600000000, 700000000]),
     ("unpack", "SU3_R12_F64", 384, 576, [130000000]),
 ]
 CASES = [(op, form, na, nc, limit, past) for op, form, na, nc, limits in CASES

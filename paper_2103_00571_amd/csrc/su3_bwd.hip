@@ -189,8 +189,8 @@ __global__ __launch_bounds__(kBwdThreads) void bwd_tiles(const u4 *__restrict__ 
         const int c = 64 * i + lane, q = c / CT;
         return (ts + D * q) * CT + (c - q * CT);
     };
-    // Step loads: chunks past the end re-read the last chunk (in bounds;
-    // those rows store nothing and add nothing). The loads of the next step
+    // Step loads: chunks past the end re-read the last chunk (in bounds; they
+    // are cleared before use, and store nothing). The loads of the next step
     // are issued as soon as the current step sits in LDS, so they are in
     // flight while the current step is computed and stored.
     u4 va[3], vg[3];
@@ -236,6 +236,16 @@ __global__ __launch_bounds__(kBwdThreads) void bwd_tiles(const u4 *__restrict__ 
             break;                              // wave-uniform
         // every row of the step's last tile is in the lattice
         const bool whole = (ts + D * (kSub - 1) + 1) * 64 <= rows;
+        // Rows past the end of the lattice hold re-read data, of another link
+        // even, and have to add exact zeros to dB: both factors are cleared,
+        // as 0 times a non-finite dC would be NaN. A row past the end is whole
+        // chunks past the end (rows come in twelves, chunks in rows or pairs).
+        if (!whole) {
+#pragma unroll
+            for (int i = 0; i < 3; ++i)
+                if (gchunk(ts, i) >= nchunks)
+                    vg[i] = va[i] = u4{0, 0, 0, 0};
+        }
 #pragma unroll
         for (int i = 0; i < 3; ++i) {
             stg[64 * i + lane] = vg[i];
@@ -260,12 +270,7 @@ __global__ __launch_bounds__(kBwdThreads) void bwd_tiles(const u4 *__restrict__ 
                 o[q][2 * m] = re;
                 o[q][2 * m + 1] = im;
             }
-            // dB(m, l) += conj(A(k, m)) dC(k, l), in FP64; rows past the end
-            // of the lattice hold re-read data and add nothing
-            const bool live = whole || (ts + D * q) * 64 + lane < rows;
-#pragma unroll
-            for (int h = 0; h < 6; ++h)
-                x[h] = live ? x[h] : S(0);
+            // dB(m, l) += conj(A(k, m)) dC(k, l), in FP64
 #pragma unroll
             for (int m = 0; m < 3; ++m)
 #pragma unroll

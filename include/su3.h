@@ -68,7 +68,7 @@
 extern "C" {
 #endif
 
-#define SU3_ABI_VERSION 7
+#define SU3_ABI_VERSION 8
 
 /* storage form codes */
 enum su3_precision {
@@ -242,15 +242,22 @@ int su3_unpack(const void *src, void *dst_f64_aos, int64_t sites, int precision,
  *   db[j](m, l)    = sum_s sum_k conj(a[s][j](k, m)) * dc[s][j](k, l)
  * da has the form of a (FP64 or FP32). db_f64 receives 4x3x3 complex double
  * (72 doubles) in every form: the site sum is accumulated in FP64 by a
- * two-stage reduction whose order depends only on `sites`, so repeated calls
- * give bit-identical db on any device. ws is device scratch of at least
+ * two-stage reduction whose order depends only on `sites` and on which of two
+ * workspace sizes ws reaches, so repeated calls give bit-identical db on any
+ * device. ws is device scratch of at least
  * su3_mult_nn_bwd_workspace_bytes(sites, precision) bytes, 16-byte aligned,
- * owned by the caller, contents undefined on entry and exit.
+ * owned by the caller, contents undefined on entry and exit. With at least
+ * su3_mult_nn_bwd_workspace_best_bytes (up to 4 times as much below 65,536
+ * sites, up to 2 times between 131,073 and 800,000 FP64 sites, else the same)
+ * a small lattice spreads over more of the chip: 6.3 against 8.1 us at 4,096
+ * FP64 sites. Either size, once large enough for a lattice, is large enough
+ * for any smaller one.
  * da must not overlap a, b or dc; db_f64 and ws must not overlap anything.
  * sites == 0: a, b, dc, da and ws may be NULL; one kernel writes db = 0.
  * Errors: as su3_mult_nn, plus SU3_ERR_WORKSPACE.
  */
 size_t su3_mult_nn_bwd_workspace_bytes(int64_t sites, int precision);
+size_t su3_mult_nn_bwd_workspace_best_bytes(int64_t sites, int precision);
 int su3_mult_nn_bwd(const void *a, const void *b, const void *dc, void *da,
                     double *db_f64, int64_t sites, int precision, void *ws,
                     size_t ws_bytes, void *stream);
@@ -262,7 +269,7 @@ int su3_mult_nn_bwd(const void *a, const void *b, const void *dc, void *da,
  * may be NULL, for callers that hold a fixed (the lattice is data, the four
  * matrices are fitted to it): then a and dc are read, nothing per site is
  * written, and b is not used and may be NULL; db is then summed in another
- * fixed order, equally a function of `sites` only. (da alone is su3_mult_na of
+ * order, fixed in the same way. (da alone is su3_mult_na of
  * dc and b.) db needs 8-byte (SU3_F64) or 4-byte (SU3_F32) alignment.
  * Otherwise arguments, workspace, zero sites and errors are as su3_mult_nn_bwd.
  */
@@ -277,7 +284,8 @@ int su3_mult_nn_grad(const void *a, const void *b, const void *dc, void *da, voi
  * fixed array of SU3_BWD_SCRATCH_BYTES (64 MiB) in the library's device
  * memory, one per device, kept until the process ends; the call itself
  * allocates nothing. Arguments, results (bit for bit) and errors are those of
- * su3_mult_nn_bwd without ws and ws_bytes, except that SU3_ERR_WORKSPACE
+ * su3_mult_nn_bwd with the larger workspace, without ws and ws_bytes, except
+ * that SU3_ERR_WORKSPACE
  * means the lattice needs more workspace than the array holds:
  * su3_mult_nn_bwd_workspace_bytes(sites, precision) > SU3_BWD_SCRATCH_BYTES,
  * i.e. above about 7.4 million sites (an L = 48 lattice, 5,308,416 sites,

@@ -17,7 +17,7 @@ _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.environ.get("SU3_LIB_PATH") or os.path.join(_HERE, "libsu3.so")
 
 # su3.h constants
-ABI_VERSION = 7
+ABI_VERSION = 8
 SU3_F64, SU3_F32, SU3_BF16, SU3_R12_F32, SU3_R12C_F32, SU3_R12_F64 = 0, 1, 2, 3, 4, 5
 SU3_OK = 0
 SU3_ERR_NULL, SU3_ERR_SIZE, SU3_ERR_ALIGN, SU3_ERR_PRECISION = -1, -2, -3, -4
@@ -43,6 +43,7 @@ SIGNATURES = {
     "su3_pack": ([_P, _P, _I64, _I, _P], _I),
     "su3_unpack": ([_P, _P, _I64, _I, _P], _I),
     "su3_mult_nn_bwd_workspace_bytes": ([_I64, _I], _SZ),
+    "su3_mult_nn_bwd_workspace_best_bytes": ([_I64, _I], _SZ),
     "su3_mult_nn_bwd": ([_P, _P, _P, _P, _P, _I64, _I, _P, _SZ, _P], _I),
     "su3_mult_nn_grad": ([_P, _P, _P, _P, _P, _I64, _I, _P, _SZ, _P], _I),
     "su3_mult_nn_bwd_noalloc": ([_P, _P, _P, _P, _P, _I64, _I, _P], _I),
@@ -153,6 +154,10 @@ def su3_unpack(src: int, dst: int, sites: int, precision: int, stream: int) -> i
 
 def su3_mult_nn_bwd_workspace_bytes(sites: int, precision: int) -> int:
     return lib.su3_mult_nn_bwd_workspace_bytes(sites, precision)
+
+
+def su3_mult_nn_bwd_workspace_best_bytes(sites: int, precision: int) -> int:
+    return lib.su3_mult_nn_bwd_workspace_best_bytes(sites, precision)
 
 
 def su3_mult_nn_bwd(a: int, b: int, dc: int, da: int, db_f64: int, sites: int, precision: int,

@@ -295,33 +295,44 @@ int su3_unpack(const void *src, void *dst_f64_aos, int64_t sites, int precision,
     return convert(src, dst_f64_aos, sites, precision, false, stream);
 }
 
-size_t su3_mult_nn_bwd_workspace_bytes(int64_t sites, int precision)
+static size_t bwd_workspace(int64_t sites, int precision, bool spread)
 {
     if (precision != SU3_F64 && precision != SU3_F32)
         return 0;
     if (sites <= 0 || sites > kMaxSites)
         return 0;
-    return (size_t)bwd_workspace_doubles(sites, precision) * sizeof(double);
+    return (size_t)bwd_workspace_doubles(sites, precision, spread) * sizeof(double);
+}
+
+size_t su3_mult_nn_bwd_workspace_bytes(int64_t sites, int precision) { return bwd_workspace(sites, precision, false); }
+
+size_t su3_mult_nn_bwd_workspace_best_bytes(int64_t sites, int precision)
+{
+    return bwd_workspace(sites, precision, true);
 }
 
 // Validation shared by the adjoint entry points. ws is the caller's workspace
 // (checked for size, alignment and overlap) unless own_ws is set, in which
 // case the library's own array is used and only its size is checked. db holds
-// db_bytes bytes; with want_da false, b and da are not used.
+// db_bytes bytes; with want_da false, b and da are not used. *spread: the
+// workspace holds su3_mult_nn_bwd_workspace_best_bytes clear of the other
+// arguments, so that the forms that need as much may run.
 static int check_bwd(const void *a, const void *b, const void *dc, const void *da, const void *db, int64_t db_bytes,
-                     bool want_da, int64_t sites, int precision, const void *ws, size_t ws_bytes, bool own_ws)
+                     bool want_da, int64_t sites, int precision, const void *ws, size_t ws_bytes, bool own_ws,
+                     bool *spread)
 {
     if (precision != SU3_F64 && precision != SU3_F32)
         return SU3_ERR_PRECISION;
     Form f;
     form_of(precision, f);
-    if (sites < 0 || sites > kMaxSites || !grid_fits(bwd_groups(sites, precision), bwd_block_threads()))
+    if (sites < 0 || sites > kMaxSites || !grid_fits(bwd_groups(sites, precision, true), bwd_block_threads()))
         return SU3_ERR_SIZE;
     if (!db)
         return SU3_ERR_NULL;
     if (sites > 0 && (!a || !dc || (want_da && (!b || !da))))
         return SU3_ERR_NULL;
-    const size_t need = su3_mult_nn_bwd_workspace_bytes(sites, precision);
+    const size_t need = bwd_workspace(sites, precision, false), best = bwd_workspace(sites, precision, true);
+    *spread = own_ws ? best <= kScratchBytes : ws_bytes >= best;
     if (own_ws) {
         if (need > kScratchBytes)
             return SU3_ERR_WORKSPACE;
@@ -341,45 +352,52 @@ static int check_bwd(const void *a, const void *b, const void *dc, const void *d
     if (want_da && (overlap(da, n, a, n) || overlap(da, n, dc, n) || overlap(da, n, b, f.b_total) ||
                     overlap(db, db_bytes, da, n) || overlap(db, db_bytes, b, f.b_total)))
         return SU3_ERR_OVERLAP;
-    if (!own_ws && (overlap(ws, (int64_t)need, a, n) || overlap(ws, (int64_t)need, dc, n) ||
-                    overlap(ws, (int64_t)need, db, db_bytes)))
+    auto ws_overlaps = [&](size_t bytes) {
+        const int64_t w = (int64_t)bytes;
+        return overlap(ws, w, a, n) || overlap(ws, w, dc, n) || overlap(ws, w, db, db_bytes) ||
+               (want_da && (overlap(ws, w, da, n) || overlap(ws, w, b, f.b_total)));
+    };
+    if (!own_ws && ws_overlaps(need))
         return SU3_ERR_OVERLAP;
-    if (!own_ws && want_da && (overlap(ws, (int64_t)need, da, n) || overlap(ws, (int64_t)need, b, f.b_total)))
-        return SU3_ERR_OVERLAP;
+    if (!own_ws && *spread && ws_overlaps(best))
+        *spread = false;
     return SU3_OK;
 }
 
 int su3_mult_nn_bwd(const void *a, const void *b, const void *dc, void *da, double *db_f64, int64_t sites,
                     int precision, void *ws, size_t ws_bytes, void *stream)
 {
-    const int st = check_bwd(a, b, dc, da, db_f64, 576, true, sites, precision, ws, ws_bytes, false);
+    bool spread = false;
+    const int st = check_bwd(a, b, dc, da, db_f64, 576, true, sites, precision, ws, ws_bytes, false, &spread);
     if (st != SU3_OK)
         return st;
     hipStream_t s = (hipStream_t)stream;
     if (sites == 0)
         return status_of(launch_bwd_zero(db_f64, false, s));
-    return status_of(launch_bwd(a, b, dc, da, db_f64, false, sites, precision, (double *)ws, s));
+    return status_of(launch_bwd(a, b, dc, da, db_f64, false, sites, precision, spread, (double *)ws, s));
 }
 
 int su3_mult_nn_grad(const void *a, const void *b, const void *dc, void *da, void *db, int64_t sites, int precision,
                      void *ws, size_t ws_bytes, void *stream)
 {
     const bool f32 = precision == SU3_F32;
+    bool spread = false;
     const int st =
-        check_bwd(a, b, dc, da, db, f32 ? 288 : 576, da != nullptr, sites, precision, ws, ws_bytes, false);
+        check_bwd(a, b, dc, da, db, f32 ? 288 : 576, da != nullptr, sites, precision, ws, ws_bytes, false, &spread);
     if (st != SU3_OK)
         return st;
     hipStream_t s = (hipStream_t)stream;
     if (sites == 0)
         return status_of(launch_bwd_zero(db, f32, s));
-    return status_of(da ? launch_bwd(a, b, dc, da, db, f32, sites, precision, (double *)ws, s)
-                        : launch_db(a, dc, db, f32, sites, precision, (double *)ws, s));
+    return status_of(da ? launch_bwd(a, b, dc, da, db, f32, sites, precision, spread, (double *)ws, s)
+                        : launch_db(a, dc, db, f32, sites, precision, spread, (double *)ws, s));
 }
 
 int su3_mult_nn_bwd_noalloc(const void *a, const void *b, const void *dc, void *da, double *db_f64, int64_t sites,
                             int precision, void *stream)
 {
-    const int st = check_bwd(a, b, dc, da, db_f64, 576, true, sites, precision, nullptr, 0, true);
+    bool spread = false;
+    const int st = check_bwd(a, b, dc, da, db_f64, 576, true, sites, precision, nullptr, 0, true, &spread);
     if (st != SU3_OK)
         return st;
     hipStream_t s = (hipStream_t)stream;
@@ -389,7 +407,7 @@ int su3_mult_nn_bwd_noalloc(const void *a, const void *b, const void *dc, void *
     const hipError_t e = bwd_scratch(&ws);
     if (e != hipSuccess)
         return SU3_ERR_HIP;
-    return status_of(launch_bwd(a, b, dc, da, db_f64, false, sites, precision, ws, s));
+    return status_of(launch_bwd(a, b, dc, da, db_f64, false, sites, precision, spread, ws, s));
 }
 
 int su3_stream_copy(const void *src, void *dst, int64_t bytes, void *stream)

@@ -32,8 +32,8 @@
 // last workgroup of the quad to arrive. Both levels keep every load of a
 // thread in flight at once, so stage 2 costs a few microseconds at any
 // lattice size.
-// The number of workgroups of every stage depends only on the number of sites
-// and the form, so the rounding sequence, and every bit of dB, is the same on
+// The number of workgroups of every stage depends only on the number of sites,
+// the precision and which of two sizes the workspace has, so the rounding sequence, and every bit of dB, is the same on
 // every run and every device. The only atomics are stage 2's arrival counts,
 // which decide who adds the run sums, not in which order.
 #include "su3_internal.hpp"
@@ -62,6 +62,12 @@ struct BwdForm {
     static constexpr bool kEarly = kEarly_, kGroup = kGroup_;
     static constexpr int kTiles = kBwdWaves * kSub * kSteps;   // 64-row tiles per workgroup
 };
+// 64-row tiles per workgroup of the forms that the smallest workspace holds the
+// partials of; the others (`spread`) take 3 or 6, and need up to 4 times as much.
+// Spreading through more wavefronts per workgroup instead, 12 of one step or 6
+// of two on 12 tiles, needs no more but loses what it is for: FP64 4,096 sites
+// 8.1 us against 6.3, 20,000 12.8 against 10.8, 160,000 55 against 50.
+constexpr int kCompactTiles = 12;
 // Which form takes which lattice, by the last site count of each (sweeps of 1,
 // 2 and 4 steps, caps of 9 and 12, batches of 0 and 256 and both kEarly at 16
 // sizes; microseconds, both stages, against 4 steps, a cap of 9 and a batch of
@@ -78,12 +84,12 @@ struct BwdForm {
 // 5%, as does a run-time choice of the order. Groups of 2 to 64, and batches of
 // 128 and 512 with them, were level or slower, and one contiguous eighth of
 // the groups per XCD 4-8% slower.
-typedef BwdForm<double, 1, 1, 0, true, 12> BwdF64x1;            // to 16,384 sites
-typedef BwdForm<double, 1, 2, 256, true, 12> BwdF64x2;          // to 32,768
-typedef BwdForm<double, 1, 4, 256, true, 9> BwdF64x4;           // to 131,072
-typedef BwdForm<double, 1, 2, 256, true, 12, true> BwdF64x2g;   // to 400,000
+typedef BwdForm<double, 1, 1, 0, true, 12> BwdF64x1;            // spread, to 16,384 sites
+typedef BwdForm<double, 1, 2, 256, true, 12> BwdF64x2;          // spread, to 32,768
+typedef BwdForm<double, 1, 4, 256, true, 9> BwdF64x4;           // to 131,072; compact, to 400,000
+typedef BwdForm<double, 1, 2, 256, true, 12, true> BwdF64x2g;   // spread, to 400,000
 typedef BwdForm<double, 1, 4, 256, true, 9, true> BwdF64x4g;    // above
-typedef BwdForm<float, 2, 1, 0, true, 12> BwdF32x1;             // to 32,768
+typedef BwdForm<float, 2, 1, 0, true, 12> BwdF32x1;             // spread, to 32,768
 typedef BwdForm<float, 2, 2, 256, true, 12> BwdF32x2;           // to 700,000
 typedef BwdForm<float, 2, 2, 0, false, 12, true> BwdF32x2g;     // above
 // dB alone (kSteps 0: the step count is a launch argument, db_steps).
@@ -443,9 +449,15 @@ __global__ __launch_bounds__(128) void bwd_zero(T *__restrict__ db)
         db[threadIdx.x] = T(0);
 }
 
+static_assert(BwdF64x4::kTiles == kCompactTiles && BwdF64x4g::kTiles == kCompactTiles &&
+                  BwdF32x2::kTiles == kCompactTiles && BwdF32x2g::kTiles == kCompactTiles,
+              "the compact forms have one count of partials");
+
 // The 64-row tiles of one workgroup of stage 1 for a lattice of n sites.
-static int64_t tiles_per_group(int64_t n, int precision)
+static int64_t tiles_per_group(int64_t n, int precision, bool spread)
 {
+    if (!spread)
+        return kCompactTiles;
     if (precision == 0)
         return n <= kLast64[0]   ? BwdF64x1::kTiles
                : n <= kLast64[1] ? BwdF64x2::kTiles
@@ -455,10 +467,10 @@ static int64_t tiles_per_group(int64_t n, int precision)
     return n <= kLast32[0] ? BwdF32x1::kTiles : n <= kLast32[1] ? BwdF32x2::kTiles : BwdF32x2g::kTiles;
 }
 
-// Workgroups of stage 1 for `sites` (a function of the size and form only).
-int64_t bwd_groups(int64_t sites, int precision)
+// Workgroups of stage 1 for `sites`, spread or not.
+int64_t bwd_groups(int64_t sites, int precision, bool spread)
 {
-    const int64_t tiles = (sites * kRowsPerSite + 63) / 64, per = tiles_per_group(sites, precision);
+    const int64_t tiles = (sites * kRowsPerSite + 63) / 64, per = tiles_per_group(sites, precision, spread);
     return (tiles + per - 1) / per;
 }
 
@@ -483,13 +495,13 @@ static int db_steps(int64_t sites, int precision)
 // 18 counts (4 bytes each) there. A form with fewer steps makes more groups,
 // so the groups do not grow with the sites everywhere; the workspace does, and
 // one that is large enough for a lattice is large enough for any smaller one.
-int64_t bwd_workspace_doubles(int64_t sites, int precision)
+int64_t bwd_workspace_doubles(int64_t sites, int precision, bool spread)
 {
-    int64_t groups = bwd_groups(sites, precision);
+    int64_t groups = bwd_groups(sites, precision, spread);
     auto at_least = [&](const int64_t *last, int count) {
         for (int i = 0; i < count; ++i)
-            if (last[i] < sites && bwd_groups(last[i], precision) > groups)
-                groups = bwd_groups(last[i], precision);
+            if (last[i] < sites && bwd_groups(last[i], precision, spread) > groups)
+                groups = bwd_groups(last[i], precision, spread);
     };
     if (precision == 0)
         at_least(kLast64, sizeof(kLast64) / sizeof(kLast64[0]));
@@ -522,30 +534,34 @@ static hipError_t launch_sum(double *ws, uint32_t *counts, int64_t groups, void 
 }
 
 hipError_t launch_bwd(const void *a, const void *b, const void *dc, void *da, void *db, bool db_float, int64_t sites,
-                      int precision, double *ws, hipStream_t s)
+                      int precision, bool spread, double *ws, hipStream_t s)
 {
-    const int64_t groups = bwd_groups(sites, precision);
+    const int64_t groups = bwd_groups(sites, precision, spread);
     uint32_t *counts = reinterpret_cast<uint32_t *>(ws + 72 * groups);
-    auto *launch = precision != 0 ? (sites <= kLast32[0]   ? launch_tiles_f<BwdF32x1, true>
-                                     : sites <= kLast32[1] ? launch_tiles_f<BwdF32x2, true>
-                                                           : launch_tiles_f<BwdF32x2g, true>)
-                   : sites <= kLast64[0] ? launch_tiles_f<BwdF64x1, true>
-                   : sites <= kLast64[1] ? launch_tiles_f<BwdF64x2, true>
-                   : sites <= kLast64[2] ? launch_tiles_f<BwdF64x4, true>
-                   : sites <= kLast64[3] ? launch_tiles_f<BwdF64x2g, true>
-                                         : launch_tiles_f<BwdF64x4g, true>;
+    auto *launch = precision != 0 ? (spread && sites <= kLast32[0] ? launch_tiles_f<BwdF32x1, true>
+                                     : sites <= kLast32[1]         ? launch_tiles_f<BwdF32x2, true>
+                                                                   : launch_tiles_f<BwdF32x2g, true>)
+                   : sites > kLast64[3]                        ? launch_tiles_f<BwdF64x4g, true>
+                   : !spread                                   ? launch_tiles_f<BwdF64x4, true>
+                   : sites <= kLast64[0]                       ? launch_tiles_f<BwdF64x1, true>
+                   : sites <= kLast64[1]                       ? launch_tiles_f<BwdF64x2, true>
+                   : sites <= kLast64[2]                       ? launch_tiles_f<BwdF64x4, true>
+                                                               : launch_tiles_f<BwdF64x2g, true>;
     const hipError_t e = launch(a, b, dc, da, sites, ws, counts, groups, 0, s);
     return e != hipSuccess ? e : launch_sum(ws, counts, groups, db, db_float, s);
 }
 
-// Its groups are never more than those of the whole adjoint, whose workspace
-// therefore serves it.
-hipError_t launch_db(const void *a, const void *dc, void *db, bool db_float, int64_t sites, int precision, double *ws,
-                     hipStream_t s)
+// Its groups are never more than those of the whole adjoint, spread or not, whose
+// workspace therefore serves it.
+hipError_t launch_db(const void *a, const void *dc, void *db, bool db_float, int64_t sites, int precision, bool spread,
+                     double *ws, hipStream_t s)
 {
-    const int steps = db_steps(sites, precision);
+    const int per_step = kBwdWaves * (precision == 0 ? DbF64::kSub : DbF32::kSub);
+    int steps = db_steps(sites, precision);
+    if (!spread && steps * per_step < kCompactTiles)
+        steps = kCompactTiles / per_step;
     const int64_t tiles = (sites * kRowsPerSite + 63) / 64;
-    const int64_t per = (int64_t)kBwdWaves * (precision == 0 ? DbF64::kSub : DbF32::kSub) * steps;
+    const int64_t per = (int64_t)per_step * steps;
     const int64_t groups = (tiles + per - 1) / per;
     uint32_t *counts = reinterpret_cast<uint32_t *>(ws + 72 * groups);
     const hipError_t e = (precision == 0 ? launch_tiles_f<DbF64, false> : launch_tiles_f<DbF32, false>)(

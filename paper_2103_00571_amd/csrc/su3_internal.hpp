@@ -288,14 +288,14 @@ hipError_t launch_stream_shape(const void *a, const void *b, void *c, int64_t ti
 // bwd_groups doubles, in 32-byte quads of components), stage 2 reduces them
 // in a fixed order; bwd_workspace_doubles is the workspace of both. db is
 // stored in double, or in float (rounded once) for db_float. launch_db forms
-// db alone.
-int64_t bwd_groups(int64_t sites, int precision);
-int64_t bwd_workspace_doubles(int64_t sites, int precision);
+// db alone. spread: small lattices take more workgroups, and more workspace.
+int64_t bwd_groups(int64_t sites, int precision, bool spread);
+int64_t bwd_workspace_doubles(int64_t sites, int precision, bool spread);
 int bwd_block_threads();
 hipError_t launch_bwd(const void *a, const void *b, const void *dc, void *da, void *db, bool db_float, int64_t sites,
-                      int precision, double *ws, hipStream_t s);
-hipError_t launch_db(const void *a, const void *dc, void *db, bool db_float, int64_t sites, int precision, double *ws,
-                     hipStream_t s);
+                      int precision, bool spread, double *ws, hipStream_t s);
+hipError_t launch_db(const void *a, const void *dc, void *db, bool db_float, int64_t sites, int precision, bool spread,
+                     double *ws, hipStream_t s);
 hipError_t launch_bwd_zero(void *db, bool db_float, hipStream_t s);
 // Bytes of the library-owned adjoint workspace (one static device array per
 // device) and its device address on the current device, looked up on the

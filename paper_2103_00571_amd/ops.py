@@ -271,8 +271,9 @@ def unpack(x: torch.Tensor, form: int | None = None) -> torch.Tensor:
 
 
 def mult_nn_bwd_workspace(sites: int, form: int, device: torch.device | int | None = None) -> torch.Tensor:
-    """A workspace tensor large enough for mult_nn_bwd on `sites` sites."""
-    nbytes = abi.su3_mult_nn_bwd_workspace_bytes(sites, form)
+    """A workspace tensor for mult_nn_bwd on `sites` sites, of the size with
+    which it is fastest."""
+    nbytes = abi.su3_mult_nn_bwd_workspace_best_bytes(sites, form)
     return torch.empty(max(nbytes, 16), dtype=torch.uint8, device=device)
 
 

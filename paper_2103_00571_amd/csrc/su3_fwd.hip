@@ -64,9 +64,12 @@
 
 namespace su3 {
 
-// FP32 reconstruct-12, 6 KiB of loads per wavefront: 200,000 sites 16.5 us with
-// 8 and 17.0 with 6, 2,560,000 sites 200 with 8 and 193 with 6.
-constexpr WaveCaps kCapsR12 = {{160000000, INT64_MAX}, {8, 6, 6}};
+// FP32 reconstruct-12, 6 KiB of loads per wavefront: 8 with the write-through
+// stores of small outputs (480 bytes of traffic for 288 written; 208,320 sites
+// 1.03-1.04 times the speed of 6, 329,152 sites 1.03-1.05), 6 with the nontemporal
+// ones that follow (343,744 sites 1.01-1.03 times 8, 1,000,000 1.03) and beyond
+// (2,560,000 sites 193 us against 200).
+constexpr WaveCaps kCapsR12 = {{kFitProduct / 288 * 480, INT64_MAX}, {8, 6, 6}};
 // a^H b: FP64 100,000 sites 18.7 us with 6 and 19.9 with 4, 2,560,000 sites 462
 // with 6 and 452 with 4 (FP32 231 and 227).
 constexpr WaveCaps kCapsAn = {{600000000, INT64_MAX}, {6, 4, 4}};
@@ -768,7 +771,7 @@ static hipError_t launch_aos(const void *a, const void *b, void *c, int64_t site
     const int64_t grid = aos_grid<F>(sites), bytes = sites * (F::kUnitsPerSite * (F::kIn + F::kOut) * 16);
     const LaunchPlan plan =
         launch_plan(reinterpret_cast<const void *>(fwd_aos<F, kConjB, true>), F::kCaps, bytes, kAosBlock, grid, cache);
-    const bool through = write_through(plan, sites * (F::kUnitsPerSite * F::kOut * 16), kFitProduct, bytes);
+    const bool through = write_through(plan, sites * (F::kUnitsPerSite * F::kOut * 16), kFitProduct);
     return launch_k(through ? fwd_aos<F, kConjB, true> : fwd_aos<F, kConjB, false>, dim3((unsigned)grid),
                     dim3(kAosBlock), s, plan.pad, (const u4 *)a, (const typename F::B *)b, (u4 *)c,
                     sites * F::kUnitsPerSite);

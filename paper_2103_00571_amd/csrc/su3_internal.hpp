@@ -233,21 +233,24 @@ inline LaunchPlan launch_plan(const void *kernel, const WaveCaps &caps, int64_t 
     const int k = bytes <= caps.upto[0] ? 0 : bytes <= caps.upto[1] ? 1 : 2;
     return launch_plan(kernel, caps.waves[k], block, grid, cache[k]);
 }
-// Where the stores of a grid of more than one generation write through: while
-// the outputs that a caller has in turn fit the 256 MiB Infinity Cache together
-// (`written` up to `fit`: three outputs of a product, two of a conversion,
-// which always writes a new one) they win 6-16%, and above `again` bytes of
-// traffic 0.5-2%. In between they depend on how many buffers are in turn and
-// where those lie, and the stores stay nontemporal. FP64 a b on three inputs,
-// into one new output each time and into three: 160,000 sites 26.5 and 26.8 us
-// against 29.6 and 29.4, 190,000 30.8 and 36.0 against 34.6 and 34.8; FP32 at
-// 614,656 sites 58.4 and 56.0 against 56.2. FP32 matrix-vector at 428 MB 65.1
-// and 75.7 against 69.0, at 612 MB 101 against 97.
-constexpr int64_t kFitProduct = 96000000, kFitConversion = 144000000, kThroughAgain = 600000000;
-inline bool write_through(const LaunchPlan &plan, int64_t written, int64_t fit, int64_t bytes,
-                          int64_t again = kThroughAgain)
+// Where the stores of a grid of more than one generation write through, by the
+// bytes a call writes. The lines are measured ones, from runs of 10 ms over 1, 3
+// and 10 inputs in turn, each with an output of its own or into new outputs, of
+// which two are then in turn.
+//  * Small outputs come back to a 256 MiB Infinity Cache that still holds part of
+//    them: how much depends on how many the caller has in turn, which a call
+//    cannot know. The product's line is where three outputs stop to gain (FP64,
+//    FP32, BF16, reconstruct-12 and a^H b, write-through against nontemporal: 97 MB
+//    1.10-1.13, 100 MB 1.03-1.04, 102 MB 0.99-1.02, 108 MB 0.98-0.995). With two it
+//    would lie at 150 MB (1.07-1.18 up to there), and ten lose up to 2% from 72 MB.
+//    Matrix-vector: 97 MB 1.05, 100 MB 0.99. A conversion writes a new output each
+//    time: 140 MB 1.02-1.18, 150 MB 0.98-1.05, 160 MB 0.96-1.00.
+//  * Outputs past the whole cache find nothing of it again, and write-through
+//    saves the eviction: 282 MB 0.97-1.01, 290 MB 1.00-1.03, in every form.
+constexpr int64_t kFitProduct = 100000000, kFitConversion = 144000000, kThroughAgain = 286000000;
+inline bool write_through(const LaunchPlan &plan, int64_t written, int64_t fit)
 {
-    return !plan.one_generation && (written <= fit || bytes > again);
+    return !plan.one_generation && (written <= fit || written > kThroughAgain);
 }
 // The dynamic LDS of a cap of `waves` wavefronts per CU on device `dev`,
 // computed on every call (no cache).

@@ -17,7 +17,7 @@ namespace su3 {
 constexpr WaveCaps kUnpackR12F32 = one_cap(7);
 constexpr WaveCaps kUnpackR12F64 = {{130000000, INT64_MAX}, {7, 6, 6}};
 constexpr WaveCaps kPackR12F32 = {{260000000, 1500000000}, {12, 6, 4}};
-constexpr WaveCaps kPackR12F64 = {{700000000, INT64_MAX}, {6, 4, 4}};
+constexpr WaveCaps kPackR12F64 = {{kThroughAgain / 384 * 960, INT64_MAX}, {6, 4, 4}};
 
 // The FP32 pack and unpack and the general transposes loop over their items
 // with a grid stride, on a grid of up to kOnePass workgroups: one pass for
@@ -654,7 +654,7 @@ static hipError_t launch_general(const void *src, void *dst, int64_t n, int64_t 
 //    before it is level there and 3% slower at 2^20 and 2^21). From planes,
 //    64-site tiles of 768 threads, grouped and write-through (160,000: 17.4,
 //    24^4: 32.4, 40^4: 232 / 250; 1.00 to 1.14 times the same tiles in order
-//    with nontemporal stores), which stay from 144 MB of output to 600 MB of traffic
+//    with nontemporal stores), which stay from 144 to 286 MB of output
 //    (write_through; 700,000: 67.1 against 63.9 in turn on three inputs).
 //  FP32 off lines: up to 49,152 sites the general path; above, 128-site tiles
 //    of 256 threads, to planes with the halo, two per CU (65,537: 9.3 / 10.7,
@@ -695,7 +695,7 @@ hipError_t launch_aos_soa(const void *src, void *dst, int64_t sites, int64_t pit
         return to_soa ? launch_tiles<to_soa_pairs<64, 128>, 64, 128, 0>((const f4 *)src, (f2 *)dst, n, pitch, s)
                       : launch_tiles<to_aos_pairs<64, 128>, 64, 128, 0>((const f2 *)src, (f4 *)dst, n, pitch, s);
     if (!to_soa)
-        return n * 288 <= kFitConversion || n * 576 > kThroughAgain
+        return n * 288 <= kFitConversion || n * 288 > kThroughAgain
                    ? launch_to_aos<f2, 64, 768, true, true, 0>(src, dst, n, pitch, s)
                    : launch_to_aos<f2, 64, 768, true, false, 0>(src, dst, n, pitch, s);
     return n <= 400000 && window ? launch_to_soa<f2, 64, 256, false, true, false, 3>(src, dst, n, pitch, s)
@@ -759,7 +759,7 @@ static hipError_t launch_pack_r12(const void *src, void *dst, int64_t links, hip
                     bytes, 64, grid, cache);
     // FP32 rows, a third of the bytes read, gain at every size
     const bool through =
-        write_through(plan, links * (6 * (int)sizeof(V)), sizeof(V) == 8 ? INT64_MAX : kFitConversion, bytes);
+        write_through(plan, links * (6 * (int)sizeof(V)), sizeof(V) == 8 ? INT64_MAX : kFitConversion);
     return launch_k(through ? pack_r12<V, true> : pack_r12<V, false>, dim3((unsigned)grid), dim3(64), s,
                     plan.pad, (const u4 *)src, (u4 *)dst, links);
 }

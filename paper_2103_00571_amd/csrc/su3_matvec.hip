@@ -20,8 +20,9 @@ namespace su3 {
 
 // Resident wavefronts per CU, each with 9.75 KiB of loads in flight; 16 fit.
 // 331,776 sites FP64: 44.3 us with 9, 42.0 with 16; 2,560,000: 323 with 7, 329
-// with 9, 343 with 16.
-constexpr WaveCaps kMvCaps = {{400000000, 1200000000}, {0, 9, 7}};
+// with 9, 343 with 16. The last line is that of the stores (816 bytes of traffic
+// for 192 written).
+constexpr WaveCaps kMvCaps = {{400000000, kThroughAgain / 192 * 816}, {0, 9, 7}};
 
 constexpr int kMvBlock = 64;    // one wavefront per workgroup
 
@@ -130,7 +131,7 @@ static hipError_t launch_mv(const void *a, const void *v, void *w, int64_t sites
     const int64_t bytes = sites * (102 * (int)sizeof(S));
     const LaunchPlan plan =
         launch_plan(reinterpret_cast<const void *>(mat_vec<S, true>), kMvCaps, bytes, kMvBlock, grid, cache);
-    const bool through = write_through(plan, sites * (24 * (int)sizeof(S)), kFitProduct, bytes, kMvCaps.upto[1]);
+    const bool through = write_through(plan, sites * (24 * (int)sizeof(S)), kFitProduct);
     return launch_k(through ? mat_vec<S, true> : mat_vec<S, false>, dim3((unsigned)grid), dim3(kMvBlock), s, plan.pad,
                     (const u4 *)a, (const uint64_t *)v, (u4 *)w, sites);
 }

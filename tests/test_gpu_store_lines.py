@@ -1,0 +1,62 @@
+"""The products and the matrix-vector product on both sides of the output sizes at
+which their stores change policy (and the reconstruct-12 product its occupancy
+cap). The entries are integers in [-9, 9] and every value is exact in FP32, so
+each form must equal torch's complex128 product bit for bit, in BF16 rounded once
+to nearest even."""
+
+import pytest
+import torch
+
+from _gpu import dev, guards_intact, poisoned, say
+
+pytestmark = pytest.mark.gpu
+
+LINES = [100000000, 286000000]
+WRITTEN = {"f64": 576, "f32": 288, "bf16": 144, "r12_f32": 288, "r12c_f32": 192, "r12_f64": 576}
+CASES = [("nn", f) for f in WRITTEN] + [(op, f) for op in ("na", "an", "mat_vec") for f in ("f64", "f32")]
+CASES = [(op, f, line // (WRITTEN[f] // (3 if op == "mat_vec" else 1)) + past)
+         for op, f in CASES for line in LINES for past in (0, 1)]
+
+
+def _ints(shape, gen):
+    z = torch.randint(-9, 10, (*shape, 2), device=dev(), generator=gen).to(torch.float64)
+    return torch.view_as_complex(z)
+
+
+def _mm(x, y):
+    return sum(x[..., :, m, None] * y[..., None, m, :] for m in range(3))
+
+
+@pytest.mark.parametrize("op,form,sites", CASES)
+def test_either_side_of_a_line(op, form, sites):
+    from paper_2103_00571_amd import abi
+
+    say("%s %s sites=%d" % (op, form, sites))
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(sites)
+    rows = 2 if form.startswith("r12") else 3
+    a = _ints((sites, 4, rows, 3), gen)
+    b = _ints((4, 3, 3), gen)
+    if op == "mat_vec":
+        b = _ints((sites, 3), gen)
+        want = _mm(a, b[:, None, :, None])[..., 0]
+    else:
+        full = a
+        if rows == 2 and form != "r12c_f32":
+            full = torch.cat([a, torch.linalg.cross(a[:, :, 0], a[:, :, 1]).conj().resolve_conj()[:, :, None]], dim=2)
+        bh = b.transpose(-1, -2).conj().resolve_conj()
+        want = (_mm(full.transpose(-1, -2).conj().resolve_conj(), b) if op == "an"
+                else _mm(full, bh if op == "na" else b))
+    wide = torch.complex128 if form.endswith("f64") else torch.complex64
+    x, y, want = a.to(wide), b.to(wide), want.to(wide)
+    if form == "bf16":
+        x = torch.view_as_real(x).to(torch.bfloat16)
+        want = torch.view_as_real(want).to(torch.bfloat16)
+    del a
+    out, whole = poisoned(want.shape, want.dtype)
+    args = (x.data_ptr(), y.data_ptr(), out.data_ptr(), sites, getattr(abi, "SU3_" + form.upper()),
+            torch.cuda.current_stream().cuda_stream)
+    assert getattr(abi, "su3_mat_vec" if op == "mat_vec" else "su3_mult_" + op)(*args) == 0
+    torch.cuda.synchronize()
+    assert torch.equal(out, want)
+    assert guards_intact(whole)

@@ -11,12 +11,12 @@ namespace su3 {
 // FP64 rows. The unpack has 9 KiB of stores and 3 or 6 KiB of loads per
 // wavefront (FP64, 100,000 sites: 16.1 us with 7 and 16.7 with 6, 2,560,000: 391
 // and 385). The pack has 9 KiB of loads (FP32, 100,000 sites: 13.6 with 12 and
-// 14.5 with 6; 1,200,000: 143 with 6, 152 with 4, 148 with 12; 2,560,000: 303
-// with 6, 298 with 4; FP64, 200,000: 28.8 with 6, 29.8 with 4; 2,560,000: 377
+// 14.5 with 6; from 1,000,000, with nontemporal stores, 5% faster with 6 than
+// with 4; FP64, 200,000: 28.8 with 6, 29.8 with 4; 2,560,000, write-through: 377
 // and 367).
 constexpr WaveCaps kUnpackR12F32 = one_cap(7);
 constexpr WaveCaps kUnpackR12F64 = {{130000000, INT64_MAX}, {7, 6, 6}};
-constexpr WaveCaps kPackR12F32 = {{260000000, 1500000000}, {12, 6, 4}};
+constexpr WaveCaps kPackR12F32 = {{260000000, INT64_MAX}, {12, 6, 6}};
 constexpr WaveCaps kPackR12F64 = {{kThroughAgain / 384 * 960, INT64_MAX}, {6, 4, 4}};
 
 // The FP32 pack and unpack and the general transposes loop over their items
@@ -417,7 +417,10 @@ __global__ __launch_bounds__(64) void pack_r12(const u4 *__restrict__ src, u4 *_
     for (int q = 0; q < 6; ++q)
         out[q] = o[q];
     wave_sync();
-    store_runs<kThrough, kOut>(dst, stage, t * 64 * kOut, lane, nout);
+    if constexpr (kThrough)
+        store_runs<true, kOut>(dst, stage, t * 64 * kOut, lane, nout);
+    else
+        store_each<kOut>(dst, stage, t * 64 * kOut, lane, nout);
 }
 
 // ------------------------------------------------------------ unpack
@@ -757,9 +760,10 @@ static hipError_t launch_pack_r12(const void *src, void *dst, int64_t links, hip
     const LaunchPlan plan =
         launch_plan(reinterpret_cast<const void *>(pack_r12<V, true>), sizeof(V) == 8 ? kPackR12F32 : kPackR12F64,
                     bytes, 64, grid, cache);
-    // FP32 rows, a third of the bytes read, gain at every size
-    const bool through =
-        write_through(plan, links * (6 * (int)sizeof(V)), sizeof(V) == 8 ? INT64_MAX : kFitConversion);
+    // FP32 rows, a third of the bytes read, do not gain again past the cache (290
+    // MB written 0.98, 1 GB 0.99)
+    const bool through = write_through(plan, links * (6 * (int)sizeof(V)), kFitConversion,
+                                       sizeof(V) == 8 ? INT64_MAX : kThroughAgain);
     return launch_k(through ? pack_r12<V, true> : pack_r12<V, false>, dim3((unsigned)grid), dim3(64), s,
                     plan.pad, (const u4 *)src, (u4 *)dst, links);
 }

@@ -103,19 +103,10 @@ __global__ __launch_bounds__(kMvBlock) void mat_vec(const u4 *__restrict__ a, co
         stage[3 * lane + i] = __builtin_bit_cast(u4, c);
     }
     wave_sync();
-    if constexpr (kThrough) {
+    if constexpr (kThrough)
         store_runs<true, 3>(w, stage, t * 192, lane, nw);
-    } else {
-        // store by store: 1-2% faster here than store_runs with nontemporal
-        // stores (750,000 sites FP64 96.9 us against 98.7)
-        const bool whole = (t + 1) * 64 <= units;
-#pragma unroll
-        for (int i = 0; i < 3; ++i) {
-            const int64_t g = t * 192 + 64 * i + lane;
-            if (whole || g < nw)
-                st_stream(w + g, stage[64 * i + lane]);
-        }
-    }
+    else
+        store_each<3>(w, stage, t * 192, lane, nw);
 }
 
 int64_t mat_vec_grid(int precision, int64_t sites)

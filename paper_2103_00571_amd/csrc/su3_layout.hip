@@ -19,6 +19,10 @@ constexpr WaveCaps kUnpackR12F64 = {{130000000, INT64_MAX}, {7, 6, 6}};
 constexpr WaveCaps kPackR12F32 = {{260000000, INT64_MAX}, {12, 6, 6}};
 constexpr WaveCaps kPackR12F64 = {{kThroughAgain / 384 * 960, INT64_MAX}, {6, 4, 4}};
 
+// Bytes written by the reconstruct-12 unpack up to which, and with FP32 rows past
+// which, its stores write through (launch_unpack_r12).
+constexpr int64_t kFitUnpackR12 = 155000000, kThroughAgainUnpackR12 = 750000000;
+
 // The FP32 pack and unpack and the general transposes loop over their items
 // with a grid stride, on a grid of up to kOnePass workgroups: one pass for
 // all but the largest lattices, which streams faster than fewer workgroups
@@ -350,10 +354,10 @@ __global__ __launch_bounds__(B) void pack_f32(const d2 *__restrict__ src, f2 *__
 // 32 bytes: 2^20 sites took 124 (pack) and 126 us (unpack), now 113 and 116;
 // 24^4 sites 42 and 45, now 37 and 38. The caps are from a sweep of 8 to 20
 // wavefronts per CU, or none, at 49,152 to 2,560,000 sites; three or four
-// chunks per lane, 256 threads and the XCD order were slower. A grid that is
-// resident at once (not kThrough) loads cached: its input is small enough to
-// be found in the caches, and nontemporal loads cost the pack of 16,384 sites
-// 15% there.
+// chunks per lane, 256 threads and the XCD order were slower. Without kThrough
+// the loads are cached: the input of a grid that is resident at once is small
+// enough to be found in the caches, and nontemporal loads cost the pack of 16,384
+// sites 15% there.
 #ifndef SU3_WAVES_BF16_CONV
 #define SU3_WAVES_BF16_CONV 14
 #endif
@@ -776,8 +780,14 @@ static hipError_t launch_unpack_r12(const void *src, void *dst, int64_t links, h
     const LaunchPlan plan =
         launch_plan(reinterpret_cast<const void *>(unpack_r12<V, true>), sizeof(V) == 8 ? kUnpackR12F32 : kUnpackR12F64,
                     links * (144 + 6 * (int)sizeof(V)), 64, grid, cache);
-    return launch_k(plan.one_generation ? unpack_r12<V, false> : unpack_r12<V, true>, dim3((unsigned)grid), dim3(64), s,
-                    plan.pad, (const u4 *)src, (u4 *)dst, links);
+    // a quarter (FP32 rows) and two fifths of the traffic are read: the first line
+    // lies a little higher than the pack's (150 MB written 1.05-1.08 and 1.00-1.05,
+    // 160 MB 1.02-1.09 and 0.97-1.01), the second where FP32 rows stop to lose when
+    // one input is unpacked again and again (450 MB 0.99, 750 MB 1.00)
+    const bool through =
+        write_through(plan, links * 144, kFitUnpackR12, sizeof(V) == 8 ? kThroughAgainUnpackR12 : kThroughAgain);
+    return launch_k(through ? unpack_r12<V, true> : unpack_r12<V, false>, dim3((unsigned)grid), dim3(64), s, plan.pad,
+                    (const u4 *)src, (u4 *)dst, links);
 }
 
 // The BF16 conversions of `chunks` 16-byte chunks of the BF16 side (9 per
@@ -809,7 +819,11 @@ static hipError_t launch_unpack_bf16(const u4 *src, d2 *dst, int64_t chunks, hip
         const int64_t grid = (m + kUnpackBf16Block - 1) / kUnpackBf16Block;
         const LaunchPlan plan = launch_plan(reinterpret_cast<const void *>(unpack_bf16<true>), SU3_WAVES_BF16_CONV,
                                             kUnpackBf16Block, grid, cache);
-        e = launch_k(plan.one_generation ? unpack_bf16<false> : unpack_bf16<true>, dim3((unsigned)grid),
+        // cached loads and nontemporal stores between the lines too: 160 MB written
+        // 1.04-1.06 and 1.37 times the plain kernel's speed with one and three inputs
+        // in turn, where write-through gives 0.97 and 1.22
+        const bool through = write_through(plan, m * 64, kFitConversion);
+        e = launch_k(through ? unpack_bf16<true> : unpack_bf16<false>, dim3((unsigned)grid),
                      dim3(kUnpackBf16Block), s, plan.pad, src + c, dst + 4 * c, m);
     }
     return e;

@@ -72,7 +72,8 @@ namespace su3 {
 constexpr WaveCaps kCapsR12 = {{kFitProduct / 288 * 480, INT64_MAX}, {8, 6, 6}};
 // a^H b: FP64 100,000 sites 18.7 us with 6 and 19.9 with 4, 2,560,000 sites 462
 // with 6 and 452 with 4 (FP32 231 and 227).
-constexpr WaveCaps kCapsAn = {{600000000, INT64_MAX}, {6, 4, 4}};
+constexpr WaveCaps kCapsAnF64 = {{600000000, INT64_MAX}, {6, 4, 4}, 75};
+constexpr WaveCaps kCapsAnF32 = {{600000000, INT64_MAX}, {6, 4, 4}, 92};
 
 constexpr int kAosBlock = SU3_AOS_BLOCK;
 // Threads per workgroup of fwd_soa: 128 measured 3% faster than 256 for FP64
@@ -151,7 +152,7 @@ __device__ __forceinline__ void pack_chunks(const S *x, u4 (&v)[N])
 // FP64: unit = output row k of link j (pos = 3j + k); 48 B in, 48 B out.
 struct FormF64 {
     static constexpr int kIn = 3, kOut = 3, kUnitsPerSite = 12;
-    static constexpr WaveCaps kCaps = one_cap(SU3_WAVES_F64);
+    static constexpr WaveCaps kCaps = one_cap(SU3_WAVES_F64, 75);
     typedef double B;
     typedef Link<double> Coef;
     __device__ static void load(const B *b, int pos, Coef &m) { load_link(b, pos / 3, m); }
@@ -168,7 +169,7 @@ struct FormF64 {
 // links; 48 B in, 48 B out.
 struct FormF32 {
     static constexpr int kIn = 3, kOut = 3, kUnitsPerSite = 6;
-    static constexpr WaveCaps kCaps = one_cap(SU3_WAVES_F32);
+    static constexpr WaveCaps kCaps = one_cap(SU3_WAVES_F32, 85);
     typedef float B;
     struct Coef {
         Link<float> m[2];
@@ -281,7 +282,7 @@ struct FormR12 {
 // rows 0-1 of a, so no row is rebuilt.
 struct FormR12C {
     static constexpr int kIn = 3, kOut = 3, kUnitsPerSite = 4;
-    static constexpr WaveCaps kCaps = one_cap(SU3_WAVES_R12C);
+    static constexpr WaveCaps kCaps = one_cap(SU3_WAVES_R12C, 85);
     typedef float B;
     typedef Link<float> Coef;
     __device__ static void load(const B *b, int pos, Coef &m) { load_link(b, pos, m); }
@@ -356,7 +357,7 @@ __device__ __forceinline__ void link_an(const S *x, const Link<S> &m, S *y)
 // 144 B in and out.
 struct FormAnF64 {
     static constexpr int kIn = 9, kOut = 9, kUnitsPerSite = 4;
-    static constexpr WaveCaps kCaps = kCapsAn;
+    static constexpr WaveCaps kCaps = kCapsAnF64;
     typedef double B;
     typedef Link<double> Coef;
     __device__ static void load(const B *b, int pos, Coef &m) { load_link(b, pos, m); }
@@ -372,7 +373,7 @@ struct FormAnF64 {
 // a^H b, FP32: unit = links 2w, 2w+1 (144 B in and out).
 struct FormAnF32 {
     static constexpr int kIn = 9, kOut = 9, kUnitsPerSite = 2;
-    static constexpr WaveCaps kCaps = kCapsAn;
+    static constexpr WaveCaps kCaps = kCapsAnF32;
     typedef float B;
     struct Coef {
         Link<float> m[2];
@@ -712,7 +713,7 @@ size_t occupancy_pad_for(const void *kernel, int waves, int block, int dev)
     return (size_t)pad;
 }
 
-LaunchPlan launch_plan(const void *kernel, int waves, int block, int64_t grid, PadCache &cache)
+LaunchPlan launch_plan(const void *kernel, int waves, int block, int64_t grid, PadCache &cache, int share)
 {
     LaunchPlan p;
     int dev = 0;
@@ -729,7 +730,7 @@ LaunchPlan launch_plan(const void *kernel, int waves, int block, int64_t grid, P
         known = (int64_t)resident << 32 | (int64_t)(occupancy_pad_for(kernel, waves, block, dev) + 1);
         cache[dev].store(known, std::memory_order_relaxed);
     }
-    p.one_generation = grid <= (known >> 32) * kCUs;
+    p.one_generation = grid <= (known >> 32) * kCUs * share / 100;
     p.pad = p.one_generation ? 0 : (size_t)((known & 0xffffffff) - 1);
     return p;
 }

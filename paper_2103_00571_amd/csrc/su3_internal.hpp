@@ -224,11 +224,18 @@ typedef std::atomic<int64_t> PadCache[kMaxDevices];
 // 8.8; BF16 at 100,000 sites 5.8 against 7.4. Past residency (reconstruct-12
 // FP64 at 69,632 sites), and past 24 wavefronts per CU where more fit (FP64
 // at 40,960 sites, FP32 at 81,920), the cap is as fast or up to 3% faster.
+// Some kernels lose that already when their last CUs fill up (`share`, the percent
+// of what is resident at once up to which a grid goes uncapped; the speed of a cap
+// alone over three inputs in turn, uncapped -> capped with write-through): FP64
+// products at 28,832 sites (88%) 0.94 -> 1.03, FP32 61,600 (94%) 0.98 -> 1.05, a^H
+// b FP32 139,264 (100%) 0.96 -> 1.04 and FP64 59,632 (91%) 0.98 -> 1.05, the
+// reconstruct-12 pack with FP64 rows 69,632 (100%) 0.97 -> 1.05. Others gain to the
+// last CU (BF16 at 99,600 sites 1.32 -> 1.06).
 struct LaunchPlan {
     size_t pad = 0;
     bool one_generation = false;
 };
-LaunchPlan launch_plan(const void *kernel, int waves, int block, int64_t grid, PadCache &cache);
+LaunchPlan launch_plan(const void *kernel, int waves, int block, int64_t grid, PadCache &cache, int share = 100);
 // Caps by the bytes a call moves: waves[0] up to upto[0], waves[1] up to
 // upto[1], waves[2] beyond, each with its own PadCache. A long stream runs best
 // with few wavefronts resident; a short one spends more of its time filling
@@ -237,16 +244,17 @@ LaunchPlan launch_plan(const void *kernel, int waves, int block, int64_t grid, P
 struct WaveCaps {
     int64_t upto[2];
     int waves[3];
+    int share = 100;
 };
-constexpr WaveCaps one_cap(int waves)
+constexpr WaveCaps one_cap(int waves, int share = 100)
 {
-    return {{INT64_MAX, INT64_MAX}, {waves, waves, waves}};
+    return {{INT64_MAX, INT64_MAX}, {waves, waves, waves}, share};
 }
 inline LaunchPlan launch_plan(const void *kernel, const WaveCaps &caps, int64_t bytes, int block, int64_t grid,
                               PadCache (&cache)[3])
 {
     const int k = bytes <= caps.upto[0] ? 0 : bytes <= caps.upto[1] ? 1 : 2;
-    return launch_plan(kernel, caps.waves[k], block, grid, cache[k]);
+    return launch_plan(kernel, caps.waves[k], block, grid, cache[k], caps.share);
 }
 // Where the stores of a grid of more than one generation write through, by the
 // bytes a call writes. The lines are measured ones, from runs of 10 ms over 1, 3

@@ -17,7 +17,7 @@ namespace su3 {
 constexpr WaveCaps kUnpackR12F32 = one_cap(7);
 constexpr WaveCaps kUnpackR12F64 = {{130000000, INT64_MAX}, {7, 6, 6}};
 constexpr WaveCaps kPackR12F32 = {{260000000, INT64_MAX}, {12, 6, 6}};
-constexpr WaveCaps kPackR12F64 = {{kThroughAgain / 384 * 960, INT64_MAX}, {6, 4, 4}};
+constexpr WaveCaps kPackR12F64 = {{kThroughAgain / 384 * 960, INT64_MAX}, {6, 4, 4}, 75};
 
 // Bytes written by the reconstruct-12 unpack up to which, and with FP32 rows past
 // which, its stores write through (launch_unpack_r12).

@@ -38,8 +38,8 @@ constexpr int64_t kOnePass = (int64_t)1 << 24;
 // LDS write (9 elements per thread), nontemporal loads and stores, and, in
 // FP64, the XCD-contiguous tile order (each XCD one contiguous eighth of the
 // tiles; a one-pass grid). The last, ragged tile moves element by element.
-// This is the path of the small lattices (and of any too large for the
-// one-pass grids below); launch_aos_soa has the rule.
+// This is the path of the small lattices (of any too large for the one-pass grids
+// below, and of some between); launch_aos_soa has the rule.
 constexpr int kTileSites = 64;
 
 template <typename V, bool kToSoa, bool kXcd>
@@ -660,9 +660,14 @@ static hipError_t launch_general(const void *src, void *dst, int64_t n, int64_t 
 //    tiles of 576 threads beyond (40^4: 234 / 257, 48^4: 516 / 558; the form
 //    before it is level there and 3% slower at 2^20 and 2^21). From planes,
 //    64-site tiles of 768 threads, grouped and write-through (160,000: 17.4,
-//    24^4: 32.4, 40^4: 232 / 250; 1.00 to 1.14 times the same tiles in order
-//    with nontemporal stores), which stay from 144 to 286 MB of output
-//    (write_through; 700,000: 67.1 against 63.9 in turn on three inputs).
+//    24^4: 32.4, 1,736,096: 157 / 159, 40^4: 232 / 250), except between 500,000 and
+//    1,450,000 sites (144 MB, where conversions stop to write through, and 418 MB
+//    of output): there the general path is on the whole faster (520,000: 49.0 /
+//    48.8, 700,000: 68.6 / 67.5, 900,000: 85.2 / 83.7, 1,400,000: 126.8 / 123.9;
+//    1,200,000: 110 / 111, 1,500,000 padded: 140 / 147), and the same tiles with
+//    nontemporal stores are 0-5% slower than it. Where a dense plane stride lies
+//    within 128 KiB of a multiple of 4 MiB its planes collide, and the tiles stay
+//    (2^20: 98 / 105).
 //  FP32 off lines: up to 49,152 sites the general path; above, 128-site tiles
 //    of 256 threads, to planes with the halo, two per CU (65,537: 9.3 / 10.7,
 //    31^4: 105 / 142, 2,560,001: 266 / 381), from planes with cached loads
@@ -701,10 +706,13 @@ hipError_t launch_aos_soa(const void *src, void *dst, int64_t sites, int64_t pit
     if (n <= 131072)
         return to_soa ? launch_tiles<to_soa_pairs<64, 128>, 64, 128, 0>((const f4 *)src, (f2 *)dst, n, pitch, s)
                       : launch_tiles<to_aos_pairs<64, 128>, 64, 128, 0>((const f2 *)src, (f4 *)dst, n, pitch, s);
-    if (!to_soa)
-        return n * 288 <= kFitConversion || n * 288 > kThroughAgain
+    if (!to_soa) {
+        const int64_t m = pitch * 8 % ((int64_t)4 << 20), near = (int64_t)128 << 10;
+        const bool collide = pitch == n && (m < near || m > ((int64_t)4 << 20) - near);
+        return n * 288 <= kFitConversion || n > 1450000 || collide
                    ? launch_to_aos<f2, 64, 768, true, true, 0>(src, dst, n, pitch, s)
-                   : launch_to_aos<f2, 64, 768, true, false, 0>(src, dst, n, pitch, s);
+                   : launch_general<f2, false>(src, dst, n, pitch, to_soa, s);
+    }
     return n <= 400000 && window ? launch_to_soa<f2, 64, 256, false, true, false, 3>(src, dst, n, pitch, s)
                                  : launch_tiles<to_soa_pairs<64, 576>, 64, 576, 0>((const f4 *)src, (f2 *)dst, n, pitch, s);
 }

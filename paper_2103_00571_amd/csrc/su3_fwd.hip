@@ -498,7 +498,9 @@ __global__ __launch_bounds__(kAosBlock) void fwd_aos(const u4 *__restrict__ a, c
 // kThrough: the output's cache policy (OutWindow). Write-through in FP32 beyond
 // one generation (dense and padded: 1.02-1.03 at 2^20 sites and above,
 // 1.08-1.10 at 24^4), never in FP64 (0.97-0.99, at any cap) or in fwd_soa_halo
-// (0.94-1.00).
+// (0.94-1.00). The nontemporal stores go to global addresses: as buffer stores they
+// took 0.4-0.8% longer in FP64 (520,000 sites dense 0.991 -> 0.998 of the speed
+// with neither, 3,200,000 padded 0.994 -> 0.998).
 template <typename V, typename S, int kWaits, bool kThrough>
 __global__ __launch_bounds__(kSoaBlock) void fwd_soa(const V *__restrict__ a, const S *__restrict__ b,
                                                   V *__restrict__ c, int64_t n, int64_t pitch, int64_t nbp, int xcd)
@@ -532,7 +534,10 @@ __global__ __launch_bounds__(kSoaBlock) void fwd_soa(const V *__restrict__ a, co
 #pragma unroll
     for (int l = 0; l < 3; ++l) {
         const V o = {re[l], im[l]};
-        st_out<kThrough>(out_window(cp + l * pitch, (n - s0) * (int64_t)sizeof(V)), threadIdx.x * sizeof(V), o);
+        if constexpr (kThrough)
+            st_out<true>(out_window(cp + l * pitch, (n - s0) * (int64_t)sizeof(V)), threadIdx.x * sizeof(V), o);
+        else
+            st_stream(cp + l * pitch + threadIdx.x, o);
     }
 }
 

@@ -290,9 +290,10 @@ int su3_mult_nn_grad(const void *a, const void *b, const void *dc, void *da, voi
  * su3_mult_nn_bwd_workspace_bytes(sites, precision) > SU3_BWD_SCRATCH_BYTES,
  * i.e. above about 7.4 million sites (an L = 48 lattice, 5,308,416 sites,
  * fits). The array's device address is looked up on the first call on each
- * device, so make that first call outside graph capture. Every call on a device shares that device's array:
- * calls that can overlap in time on one device (two streams, two host
- * threads, two graphs) race on it and must be ordered by the caller.
+ * device, so make that first call outside graph capture. Every call on a device
+ * shares that device's array: calls that can overlap in time on one device (two
+ * streams, two host threads, two graphs) race on it and must be ordered by the
+ * caller.
  */
 #define SU3_BWD_SCRATCH_BYTES ((size_t)64 << 20)
 int su3_mult_nn_bwd_noalloc(const void *a, const void *b, const void *dc, void *da,
@@ -301,10 +302,13 @@ int su3_mult_nn_bwd_noalloc(const void *a, const void *b, const void *dc, void *
 
 /*
  * Measurement aid: device-to-device copy of `bytes` bytes, one 16-byte
- * nontemporal load and store per thread over a grid that covers the buffer
- * once, the streaming pattern of the link multiply without the arithmetic. Used to
- * measure the HBM bandwidth the multiply is compared against. bytes must be
- * a multiple of 16; src and dst 16-byte aligned and non-overlapping.
+ * nontemporal load and one store per thread over a grid that covers the buffer
+ * once, the streaming pattern of the link multiply without the arithmetic. The
+ * stores write through to memory, except in copies of at most 6,291,456 bytes,
+ * whose grid is resident at once: there they are nontemporal too. Above
+ * 300,000,000 bytes at most 24 wavefronts per CU are resident.
+ * Used to measure the HBM bandwidth the multiply is compared against. bytes must
+ * be a multiple of 16; src and dst 16-byte aligned and non-overlapping.
  */
 int su3_stream_copy(const void *src, void *dst, int64_t bytes, void *stream);
 
@@ -316,14 +320,17 @@ int su3_stream_copy(const void *src, void *dst, int64_t bytes, void *stream);
  * (bytes w*1024*out ..), with one 64-thread workgroup per tile and at most
  * waves_per_cu resident wavefronts per CU (0: no cap, at most 32).
  * tile_order picks which workgroup takes which tile: 0, workgroup i takes
- * tile i (the order of su3_stream_copy, su3_mult_nn_soa and the adjoint);
- * 1, XCD-contiguous, the order of the site-major products, the matrix-vector
+ * tile i (the order of su3_stream_copy, of su3_mult_nn_soa at most plane
+ * strides, and of the adjoint up to 131,072 FP64 and 700,000 FP32 sites;
+ * larger ones take 16 consecutive workgroups' work per XCD in turn); 1,
+ * XCD-contiguous, the order of the site-major products, the matrix-vector
  * product and the reconstruct-12 pack and unpack. MI355X deals workgroups
  * round-robin to its 8 XCDs, and order 1 gives XCD x (the workgroups i with
  * i mod 8 = x) one contiguous run of tiles: with q = tiles / 8 and
- * r = tiles mod 8, its k-th workgroup takes tile x*q + min(x, r) + k. The
- * values written are the XOR of the lane's loaded chunks with the chunk
- * number added to the first word. The shapes are those of the kernels:
+ * r = tiles mod 8, its k-th workgroup takes tile x*q + min(x, r) + k. The loads
+ * are nontemporal, the stores write through. The values written are the XOR of
+ * the lane's loaded chunks with the chunk number added to the first word. The
+ * shapes are those of the kernels:
  * (in_a, in_b, out) = (1, 0, 1) copy; (3, 0, 3) the FP64/FP32/BF16 forward;
  * (3, 3, 3) the adjoint; (6, 0, 9) reconstruct-12 with full output;
  * (9, 0, 9) a^H b. Sizes: a holds tiles*1024*in_a bytes, b tiles*1024*in_b

@@ -72,8 +72,11 @@ constexpr int kCompactTiles = 12;
 // 2 and 4 steps, caps of 9 and 12, batches of 0 and 256 and both kEarly at 16
 // sizes; microseconds, both stages, against 4 steps, a cap of 9 and a batch of
 // 256 in FP64 and 2 steps and a cap of 12 in FP32, both without kEarly).
-// The lines at 16,384 to 131,072 sites lie where the whole grid is resident
-// at once with 1, 2 or 4 steps.
+// The lines at 16,384 and 32,768 sites lie where the whole grid is resident at
+// once, 4 workgroups per CU, with 1 and 2 steps. 131,072 is where the partials of 4
+// steps still are one run of stage 2 (2,048): up to there 4 steps are the faster
+// (against 2 grouped steps 65,537 sites 1.08, 98,304 1.03, 131,072 1.01), past it 2
+// (131,073 1.02-1.03, 160,000 1.02-1.03, 200,000 1.03-1.04).
 //  FP64: 4,096 sites 6.2 / 8.4, 16,384 9.6 / 10.2, 20,000 10.8 / 12.0, 131,072
 //  42.6 / 43.2, 160,000 49.9 / 52.1, 331,776 96 / 98, 2^20 288 / 292, 2,000,000
 //  542 / 556 (2 steps there: 567).
@@ -366,7 +369,10 @@ __global__ __launch_bounds__(kBwdThreads) void bwd_tiles(const u4 *__restrict__ 
 // atomics at the memory side), each store complete before the count, so no
 // cache has to be written back or invalidated; a release fence would write
 // back the XCD's whole L2 in every workgroup, which made one launch slower
-// than two. Two launches took 9.3 us (4.7 and 4.6) after stage 1 in FP64, at
+// than two. The order of sum and count rests on the hardware, not on the
+// language's memory model, which grants relaxed accesses none: a store at agent
+// scope writes through, vmcnt counts it until it has reached the memory side, and
+// the loads that follow the last arrival's count read there. Two launches took 9.3 us (4.7 and 4.6) after stage 1 in FP64, at
 // L = 32 and at 24^4 alike; this one takes 5.8 and 5.4.
 // T: the type dB is stored in, double, or float for the FP64 sum rounded once.
 template <typename T>

@@ -15,10 +15,10 @@
 //    fwd_soa_halo where the output planes start off 128-byte lines).
 //  * The grid covers the lattice once: each wavefront streams one tile and
 //    exits. In the site-major kernels each XCD takes one contiguous eighth of
-//    the tiles (xcd_tile); the SoA kernel picks its order (soa_xcd) and, in
-//    how many phases its plane loads take (soa_waits) from the plane
-//    stride, and takes any plane pitch >= the site count (soa_pitch gives
-//    the one that keeps the planes from colliding in HBM).
+//    the tiles (xcd_tile); the SoA kernel picks its order (soa_xcd) and the
+//    number of phases of its plane loads (soa_waits) from the plane stride,
+//    and takes any plane pitch >= the site count (soa_pitch gives the one
+//    that keeps the planes from colliding in HBM).
 //  * a is streamed with nontemporal 16-byte loads, c with write-through or
 //    nontemporal stores (OutWindow).
 //  * 64-bit offsets throughout (a FP64 L=48 lattice is 3.06e9 bytes).

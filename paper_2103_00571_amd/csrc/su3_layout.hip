@@ -126,11 +126,13 @@ __global__ __launch_bounds__(kBlock) void transpose_aos_soa(const V *__restrict_
 // The same transforms for the larger lattices, one tile of TS sites per
 // workgroup of B threads. What bounds them is the 36 plane streams: a kernel
 // that only copies the same addresses (36 KiB per workgroup in and out, no
-// LDS, nontemporal) peaks at 6.0 (to planes) and 6.2 TB/s (from planes) at
-// 2,560,000 FP64 sites, with one such workgroup per CU, and falls to 5.6 and
-// 5.9 with two to four; the run length on the planes (1 to 16 KiB) does not
-// matter. So the tile and the number of resident workgroups set the bytes in
-// flight, and many threads with few elements each keep a tile's life short.
+// LDS, nontemporal stores, workgroup order) peaks at 6.0 (to planes) and 6.2 TB/s
+// (from planes) at 2,560,000 FP64 sites, with one such workgroup per CU, and falls
+// to 5.6 and 5.9 with two to four; the run length on the planes (1 to 16 KiB) does
+// not matter. So the tile and the number of resident workgroups set the bytes in
+// flight, and many threads with few elements each keep a tile's life short. Write-
+// through stores in the grouped order pass that copy (6.1 and 6.3 TB/s); the bound
+// with them has not been probed.
 // launch_aos_soa states which tile serves which size.
 // kThrough: write-through stores (OutWindow) instead of nontemporal ones.
 // kGroup: the grouped tile order (group_order), which alone is worth 1-2% and
@@ -334,7 +336,9 @@ __global__ __launch_bounds__(B) void to_aos_pairs(const f2 *__restrict__ src, f4
 // FP64 complex -> FP32 complex, round to nearest even (v_cvt_f32_f64), one
 // complex per thread: 16 bytes in, 8 out. Nontemporal loads and write-through
 // stores: 6.97 against 6.49 TB/s with plain ones at 2^20 sites, 6.4 against
-// 5.9 at 160,000.
+// 5.9 at 160,000. Small grids take them too, unlike the BF16 pack's: up to 8,192
+// sites they are level (3.3 us), at 16,384 3.5 us against 3.9 over one and three
+// inputs in turn and 4.0 against 3.9 over ten, at 32,768 5.4-6.1 against 6.0-6.6.
 template <int B>
 __global__ __launch_bounds__(B) void pack_f32(const d2 *__restrict__ src, f2 *__restrict__ dst, int64_t n)
 {
@@ -429,7 +433,9 @@ __global__ __launch_bounds__(64) void pack_r12(const u4 *__restrict__ src, u4 *_
 
 // ------------------------------------------------------------ unpack
 // FP32 complex -> FP64, exact, one complex per thread; nontemporal loads and
-// stores: 6.70 against 6.47 TB/s with plain ones at 2^20 sites.
+// stores: 6.70 against 6.47 TB/s with plain ones at 2^20 sites, level up to 16,384
+// (3.4 us at 8,192, 4.4 at 16,384), 6.4-6.8 us against 6.9-7.7 at 32,768. Only one
+// input unpacked again and again at 200,000 to 280,000 sites loses (1-2.5%).
 template <int B>
 __global__ __launch_bounds__(B) void unpack_f32(const f2 *__restrict__ src, d2 *__restrict__ dst, int64_t n)
 {
@@ -555,8 +561,8 @@ __global__ __launch_bounds__(kCopyBlock) void stream_copy(const u4 *__restrict__
 // XCD-contiguous tile, xcd_order) reads chunks w*64*RA + 64 i + lane of a
 // (i < RA) and likewise of b, and writes chunks w*64*W + 64 i + lane of c,
 // the same whole-wavefront 1 KiB runs and per-lane chunk counts as the
-// kernels it stands beside and their write-through stores, with no arithmetic beyond folding the loads
-// into the stored values (so that no load is dead).
+// kernels it stands beside and their write-through stores, with no arithmetic
+// beyond folding the loads into the stored values (so that no load is dead).
 template <int RA, int RB, int W>
 __global__ __launch_bounds__(64) void stream_shape(const u4 *__restrict__ a, const u4 *__restrict__ b,
                                                    u4 *__restrict__ c, int order)
@@ -640,8 +646,9 @@ static hipError_t launch_general(const void *src, void *dst, int64_t n, int64_t 
 //    sizes, dense and padded), beyond that 576 threads, nontemporal (24^4: 64 /
 //    78; the form before it is level there and 5% slower at 2^20), and above
 //    1,100,000 sites grouped and write-through (40^4: 490 / 565, 48^4: 1018 /
-//    1150; 0.98 at 2^21 padded and 1.01 to 1.06 at 14 other sizes and pitches
-//    against nontemporal in order, 0.91 to 1.0 at 262,656 to 663,552
+//    1150; against nontemporal in order 0.98 at 2^21 padded and 1.01 to 1.07
+//    elsewhere, 2^20 * 9/8 to 2^22 * 5/4 sites, 2^22 padded 1.05 among them: no
+//    line by the plane stride follows; 0.91 to 1.0 at 262,656 to 663,552
 //    sites). Off lines, 128-site tiles with the
 //    halo, two per CU up to 131,072 sites (65,537: 13.5 / 15.9) and one
 //    above (31^4: 193 / 250, 2,560,001: 533 / 630).

@@ -24,6 +24,13 @@ def to_dev(x):
     return torch.from_numpy(np.ascontiguousarray(x)).to(dev())
 
 
+def ints(shape, gen):
+    """Complex integers with parts in [-9, 9], complex128 on the GPU: products
+    and sums of them are exact in FP64 (and, for products of links, in FP32)."""
+    z = torch.randint(-9, 10, (*shape, 2), device=dev(), generator=gen).to(torch.float64)
+    return torch.view_as_complex(z)
+
+
 def poisoned(shape, dtype):
     """An output tensor inside a larger NaN-filled buffer: returns (view,
     whole). The GUARD sites before and after the view must stay NaN."""

@@ -8,17 +8,12 @@ and the finite part must equal torch's complex128 contractions."""
 import pytest
 import torch
 
-from _gpu import dev, say
+from _gpu import dev, ints, say
 
 pytestmark = pytest.mark.gpu
 
 # a ragged count for every launch form of both precisions, and whole tiles
 SIZES = [1, 5, 15, 16, 17, 63, 8193, 16385, 32769, 100003, 131073, 400001, 700001]
-
-
-def _ints(shape, gen):
-    z = torch.randint(-9, 10, (*shape, 2), device=dev(), generator=gen).to(torch.float64)
-    return torch.view_as_complex(z)
 
 
 @pytest.mark.parametrize("dtype", [torch.complex128, torch.complex64])
@@ -29,7 +24,7 @@ def test_last_link_does_not_reach_the_others(sites, dtype):
     form = abi.SU3_F64 if dtype == torch.complex128 else abi.SU3_F32
     gen = torch.Generator(device="cuda")
     gen.manual_seed(sites)
-    a, dc, b = (_ints(s, gen) for s in ((sites, 4, 3, 3), (sites, 4, 3, 3), (4, 3, 3)))
+    a, dc, b = (ints(s, gen) for s in ((sites, 4, 3, 3), (sites, 4, 3, 3), (4, 3, 3)))
     da = sum(dc[..., :, m, None] * b.conj()[None, :, None, :, m] for m in range(3)).to(dtype)
     db = sum((a.conj()[:, :, m, :, None] * dc[:, :, m, None, :]).sum(0) for m in range(3))
     inf, nan = float("inf"), float("nan")

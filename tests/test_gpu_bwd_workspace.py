@@ -7,16 +7,11 @@ written."""
 import pytest
 import torch
 
-from _gpu import dev, say
+from _gpu import dev, ints, say
 
 pytestmark = pytest.mark.gpu
 
 SIZES = [1, 63, 4096, 8193, 16384, 16385, 24577, 32768, 32769, 131072, 131073, 400000, 400001, 700001]
-
-
-def _ints(shape, gen):
-    z = torch.randint(-9, 10, (*shape, 2), device=dev(), generator=gen).to(torch.float64)
-    return torch.view_as_complex(z)
 
 
 @pytest.mark.parametrize("dtype", [torch.complex128, torch.complex64])
@@ -28,7 +23,7 @@ def test_both_workspace_sizes(sites, dtype):
     form = abi.SU3_F64 if dtype == torch.complex128 else abi.SU3_F32
     gen = torch.Generator(device="cuda")
     gen.manual_seed(sites)
-    a, dc, b = (_ints(s, gen) for s in ((sites, 4, 3, 3), (sites, 4, 3, 3), (4, 3, 3)))
+    a, dc, b = (ints(s, gen) for s in ((sites, 4, 3, 3), (sites, 4, 3, 3), (4, 3, 3)))
     da = sum(dc[..., :, m, None] * b.conj()[None, :, None, :, m] for m in range(3)).to(dtype)
     db = sum((a.conj()[:, :, m, :, None] * dc[:, :, m, None, :]).sum(0) for m in range(3))
     a, dc, b = a.to(dtype), dc.to(dtype), b.to(dtype)

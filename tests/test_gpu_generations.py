@@ -6,7 +6,7 @@ form must equal torch's complex128 product (pack: its rows) bit for bit."""
 import pytest
 import torch
 
-from _gpu import dev, guards_intact, poisoned, say
+from _gpu import dev, guards_intact, ints, poisoned, say
 
 pytestmark = pytest.mark.gpu
 
@@ -15,11 +15,6 @@ CASES = [("nn", "f64", 32768, 75), ("na", "f64", 32768, 75), ("nn", "f32", 65536
          ("nn", "r12c_f32", 98304, 85), ("an", "f64", 65536, 75), ("an", "f32", 131072, 92), ("an", "f32", 139264, 92),
          ("pack", "r12_f64", 65536, 75), ("pack", "r12_f64", 69632, 75)]
 CASES = [(op, f, full * share // 100 + off) for op, f, full, share in CASES for off in (-16, 0, 1, 17)]
-
-
-def _ints(shape, gen):
-    z = torch.randint(-9, 10, (*shape, 2), device=dev(), generator=gen).to(torch.float64)
-    return torch.view_as_complex(z)
 
 
 def _mm(x, y):
@@ -34,7 +29,7 @@ def test_either_side_of_a_full_chip(op, form, sites):
     gen = torch.Generator(device="cuda")
     gen.manual_seed(sites)
     wide = torch.complex128 if form.endswith("f64") else torch.complex64
-    a, b = _ints((sites, 4, 2 if form == "r12c_f32" else 3, 3), gen), _ints((4, 3, 3), gen)
+    a, b = ints((sites, 4, 2 if form == "r12c_f32" else 3, 3), gen), ints((4, 3, 3), gen)
     bh = b.transpose(-1, -2).conj().resolve_conj()
     if op == "pack":
         want = a[:, :, :2].contiguous()

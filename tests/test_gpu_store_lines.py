@@ -7,7 +7,7 @@ to nearest even."""
 import pytest
 import torch
 
-from _gpu import dev, guards_intact, poisoned, say
+from _gpu import dev, guards_intact, ints, poisoned, say
 
 pytestmark = pytest.mark.gpu
 
@@ -16,11 +16,6 @@ WRITTEN = {"f64": 576, "f32": 288, "bf16": 144, "r12_f32": 288, "r12c_f32": 192,
 CASES = [("nn", f) for f in WRITTEN] + [(op, f) for op in ("na", "an", "mat_vec") for f in ("f64", "f32")]
 CASES = [(op, f, line // (WRITTEN[f] // (3 if op == "mat_vec" else 1)) + past)
          for op, f in CASES for line in LINES for past in (0, 1)]
-
-
-def _ints(shape, gen):
-    z = torch.randint(-9, 10, (*shape, 2), device=dev(), generator=gen).to(torch.float64)
-    return torch.view_as_complex(z)
 
 
 def _mm(x, y):
@@ -35,10 +30,10 @@ def test_either_side_of_a_line(op, form, sites):
     gen = torch.Generator(device="cuda")
     gen.manual_seed(sites)
     rows = 2 if form.startswith("r12") else 3
-    a = _ints((sites, 4, rows, 3), gen)
-    b = _ints((4, 3, 3), gen)
+    a = ints((sites, 4, rows, 3), gen)
+    b = ints((4, 3, 3), gen)
     if op == "mat_vec":
-        b = _ints((sites, 3), gen)
+        b = ints((sites, 3), gen)
         want = _mm(a, b[:, None, :, None])[..., 0]
     else:
         full = a
